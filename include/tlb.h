@@ -210,19 +210,17 @@ int32_t tlb_diagnostics(tlb_grid* grid, double out[2], double* phi_avg, double* 
  * torus: S(m, m') = |DFT of phi over the node grid|^2 at mode numbers m (theta) and m' (phi),
  * wavenumbers k = (m / r, m' / R) with signed mode numbers (the Nyquist mode counts as -n/2),
  * the zero mode left out; out[0] = L_S = 2 pi sum S / sum |k| S, out[1] = sum S,
- * out[2] = sum |k| S (host array of 3 doubles).  A direct DFT in FP64 (rows, then columns),
+ * out[2] = sum |k| S (host array of 3 doubles).  FFTs of any length in FP64 (rows, then columns),
  * fixed-order sums; the spinodal coarsening runs of section IV are the use.  The first call
- * allocates a workspace of about 16 n_theta n_phi bytes, kept until tlb_destroy.
+ * allocates a workspace of about 8 n_theta n_phi bytes, kept until tlb_destroy.
  * n_phi <= 8192 and n_theta <= 4096.  Waits for the stream.  Errors: TLB_EINVAL,
  * TLB_ENOMEM, TLB_EHIP.                                                                    */
 int32_t tlb_structure_length(tlb_grid* grid, double out[3]);
 
 /* tlb_structure_length without any allocation, for callers that cannot allocate device
- * memory (serving loops, code that must not call hipMalloc): the same outputs (to rounding:
- * its twiddle factors are computed on the GPU and its final sums are taken in another fixed
- * order) from a workspace that is a static device array of 24 MiB per GPU, held from the
+ * memory (serving loops, code that must not call hipMalloc): the same outputs from a workspace that is a static device array of 24 MiB per GPU, held from the
  * library's first use on that GPU until the process ends; nothing is allocated, on the device
- * or the host.  Grids need (n_theta n_phi + n_theta + n_phi) 16 + 16 n_phi + 24 bytes of it
+ * or the host.  Grids may need (n_theta n_phi + n_theta + n_phi) 16 + 16 n_phi + 24 bytes of it
  * (up to about 1.5 M nodes); larger grids get TLB_EINVAL.  Every call on one GPU uses the same
  * workspace, which keeps the last call's contents: calls that overlap on one GPU (on several
  * streams or host threads) race.  Waits for the grid's stream.  Errors: TLB_EINVAL, TLB_EHIP. */
