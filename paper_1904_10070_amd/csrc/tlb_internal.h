@@ -55,6 +55,7 @@ int32_t tlbi_fail(int32_t code, const std::string& msg);
 struct tlbi_launch {
   const void* fn;
   dim3 grid, block;
+  unsigned lds = 0;  // dynamic LDS bytes per block
   alignas(16) unsigned char args[512];
 };
 
