@@ -231,11 +231,15 @@ void tlb_destroy(tlb_grid* grid);
 
 /* Tile height of the fused stage kernel: tiles of 64 (phi) x rows (theta) nodes, one block of
  * 64 rows threads each; rows = 4, 8 (default) or 16.  Results do not depend on it (every node
- * runs the same arithmetic); only speed does.  Errors: TLB_EINVAL.                          */
+ * runs the same arithmetic); only speed does.  Grids of few nodes (at most 1280 row segments of
+ * 64 nodes in precision 32, 640 in precision 64; not TLB_WENO5) are stepped by a kernel without
+ * tiles, whose results are the same; for them the height matters only in batches, which have
+ * their own.  Errors: TLB_EINVAL.                                                            */
 int32_t tlb_set_tile_rows(tlb_grid* grid, int32_t rows);
 
 /* Autotuner: time the stage kernel for every tile height on this grid (stage-1 launches,
- * which leave the state unchanged) and keep the fastest; *rows (may be NULL) receives it.
+ * which leave the state unchanged) and keep the fastest; *rows (may be NULL) receives it (grids
+ * stepped without tiles keep the height they have).
  * Waits for the stream.  Errors: TLB_EINVAL, TLB_EHIP.                                     */
 int32_t tlb_autotune(tlb_grid* grid, int32_t* rows);
 

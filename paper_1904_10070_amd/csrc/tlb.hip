@@ -121,6 +121,21 @@ struct Tile {
 };
 constexpr int DEFAULT_TY = 8;
 
+// The arithmetic that the tile and the small-grid kernel share is written with explicit fused
+// multiply-adds and the compiler's own contraction off, so that both round alike.
+#define TLB_EXPLICIT_FMA _Pragma("clang fp contract(off)")
+template <typename T>
+__device__ __forceinline__ T fused(T a, T b, T c) {
+  if constexpr (std::is_same<T, float>::value) return __builtin_fmaf(a, b, c);
+  else return __builtin_fma(a, b, c);
+}
+// a b + c d
+template <typename T>
+__device__ __forceinline__ T products(T a, T b, T c, T d) {
+  TLB_EXPLICIT_FMA
+  return fused(a, b, c * d);
+}
+
 // UW5 flux difference (face_{+1/2} - face_{-1/2}) for a positive velocity, offsets -3..+2;
 // the negative-velocity stencil is its mirror image with the sign flipped, offsets -2..+3.
 __host__ __device__ constexpr double uw5p(int o) {
@@ -128,6 +143,41 @@ __host__ __device__ constexpr double uw5p(int o) {
        : o == 0 ? 20.0 / 60 : o == 1 ? 30.0 / 60 : o == 2 ? -3.0 / 60 : 0.0;
 }
 __host__ __device__ constexpr double uw5m(int o) { return -uw5p(-o); }
+
+// sum_o uw5(o) f(o) for v > 0 (POS) or v < 0, the first two values together, then in the order of
+// the offsets
+template <typename T, bool POS, class F>
+__device__ __forceinline__ T uw5_difference(F f) {
+  TLB_EXPLICIT_FMA
+  T d = POS ? products(T(uw5p(-2)), f(-2), T(uw5p(-3)), f(-3))
+            : products(T(uw5m(-2)), f(-2), T(uw5m(-1)), f(-1));
+  static_for<(POS ? -1 : 0), (POS ? 3 : 4)>([&](auto oc) {
+    constexpr int o = decltype(oc)::value;
+    d = fused(T(POS ? uw5p(o) : uw5m(o)), f(o), d);
+  });
+  return d;
+}
+
+// The advection of population (i, j), -v_i/(r J) d_theta (J f) - v_j/J d_phi f, from dth, the
+// J-weighted theta difference of the stored values, and dph, their phi difference.  With deviation
+// storage the constant n_ref w_i w_j drops out of the phi differences (their weights sum to zero)
+// but not out of the J-weighted theta differences: `constant` = n_ref w_i w_j, bsum the sum of the
+// theta weights.  (Which products are fused is a matter of rounding only; it is kept as it always
+// was, so that FP32 states repeat bit for bit.)
+template <typename T>
+__device__ __forceinline__ T advection(bool theta_first, bool fuse_constant, T dth, T dph, T vi,
+                                       T vj_Jdph, T constant, T bsum) {
+  TLB_EXPLICIT_FMA
+  if constexpr (stores_deviation<T>())
+    dth = fuse_constant ? fused(constant, bsum, dth) : dth + constant * bsum;
+  return theta_first ? products(-vi, dth, vj_Jdph, dph) : products(vj_Jdph, dph, -vi, dth);
+}
+__host__ __device__ constexpr bool theta_first(int i, int j) { return i < 2 && j >= 2; }
+// the first use of each constant's product with bsum (w_i w_j takes three values; i < 2 and i >= 2)
+__host__ __device__ constexpr bool fuse_constant(int i, int j) {
+  const int k = 4 * i + j;
+  return k == 0 || k == 1 || k == 5 || k == 8 || k == 9 || k == 12;
+}
 
 // WENO-5 face value (Jiang and Shu, J. Comput. Phys. 126, 1996) between h0 and hp1 from the
 // upwind side: third-order candidates on {-2,-1,0}, {-1,0,1}, {0,1,2}, combined with weights
@@ -234,7 +284,7 @@ struct Ch4Args {
   T* P;
   T* Q;
   const RowCoef<T>* rows;
-  int nt, np;
+  int nt, np, ntx;  // ntx = ceil(np / 64)
   long long plane;
   T A, kappa, n_ref;
 };
@@ -374,15 +424,22 @@ struct TileCopy {
   }
 };
 
-// chemical potential (eq. mu) at local node (y, x) in [-1, TY] x [-1, TX] of the phi tile
+// chemical potential (eq. mu) from phi at a node and its north, south (along theta), east and west
+// (along phi) neighbours
+template <typename T>
+__device__ __forceinline__ T mu_of(T ph, T pn, T ps, T pe, T pw, const RowCoef<T>& rc, T A,
+                                   T kappa) {
+  TLB_EXPLICIT_FMA
+  const T lap = fused(rc.lap_p, fused(T(-2), ph, pe) + pw,
+                      products(rc.lap_n, pn - ph, -rc.lap_s, ph - ps));
+  return fused(A * ph, fused(ph, ph, T(-1)), -(kappa * lap));
+}
+// ... at local node (y, x) in [-1, TY] x [-1, TX] of the phi tile
 template <typename T>
 __device__ __forceinline__ T mu_at(const T* sPhi, int y, int x, const RowCoef<T>& rc, T A,
                                    T kappa) {
   const int c = (y + 2) * LXT + (x + CX);
-  const T ph = sPhi[c];
-  const T lap = rc.lap_n * (sPhi[c + LXT] - ph) - rc.lap_s * (ph - sPhi[c - LXT]) +
-                rc.lap_p * (sPhi[c + 1] - T(2) * ph + sPhi[c - 1]);
-  return A * ph * (ph * ph - T(1)) - kappa * lap;
+  return mu_of(sPhi[c], sPhi[c + LXT], sPhi[c - LXT], sPhi[c + 1], sPhi[c - 1], rc, A, kappa);
 }
 
 // population ring depth D: while a group of PB populations is used, the copies of the next
@@ -435,6 +492,98 @@ __device__ __forceinline__ T get_y0(const T* p) {
     return __builtin_nontemporal_load(p);
   else
     return *p;
+}
+
+// The interface force n F = -phi grad mu (Xth = -n F^theta, Fph = F^phi) and the Cahn-Hilliard
+// right-hand side at a node: mu at the node and its four neighbours, J u^theta phi at the north and
+// south and u^phi phi at the east and west ones.
+template <typename T>
+__device__ __forceinline__ void ch_rhs(T phc, T inv_n, const RowCoef<T>& rc, const Consts<T>& c,
+                                       T mu_c, T mu_n, T mu_s, T mu_e, T mu_w, T P_n, T P_s,
+                                       T Q_e, T Q_w, T& Xth, T& Fph, T& Lphi) {
+  TLB_EXPLICIT_FMA
+  Xth = phc * (mu_n - mu_s) * c.inv_2rdth;
+  Fph = -phc * (mu_e - mu_w) * rc.inv_2Jdph * inv_n;
+  const T lapmu = fused(rc.lap_p, fused(T(-2), mu_c, mu_e) + mu_w,
+                        products(rc.lap_n, mu_n - mu_c, -rc.lap_s, mu_c - mu_s));
+  Lphi = c.M * lapmu;
+  if (c.ch_adv) Lphi = Lphi - products(P_n - P_s, rc.inv_2rJdth, Q_e - Q_w, rc.inv_2Jdph);
+}
+
+// The same at fourth order (TLB_CH4): fourth-order central grad mu, the fourth-order surface
+// Laplacian of mu (staggered along theta: face gradients (m_{a-1} - 27 m_a + 27 m_{a+1} - m_{a+2})
+// at the faces a+1/2, a = q-2 .. q+1, weighted by J_face / (576 r^2 J dtheta^2) with
+// (1, -27, 27, -1); the five-point fourth-order difference along phi) and fourth-order central
+// flux differences.  m, mp: mu at offset o along theta and phi; P, Q: the fluxes along them.
+template <typename T, class M, class MP, class PF, class QF>
+__device__ __forceinline__ void ch4_rhs(T phc, T inv_n, const RowCoef<T>& rc, const Consts<T>& c,
+                                        M m, MP mp, PF P, QF Q, T& Xth, T& Fph, T& Lphi) {
+  auto G = [&](int o) {  // face gradient numerator at the face (q + o) + 1/2
+    return m(o - 1) - T(27) * m(o) + T(27) * m(o + 1) - m(o + 2);
+  };
+  const T dmu_th = (m(-2) - T(8) * m(-1)) + (T(8) * m(1) - m(2));
+  const T dmu_ph = (mp(-2) - T(8) * mp(-1)) + (T(8) * mp(1) - mp(2));
+  Xth = phc * dmu_th * c.inv_12rdth;
+  Fph = -phc * dmu_ph * rc.inv_12Jdph * inv_n;
+  const T lap_th = rc.l4[0] * G(-2) - T(27) * (rc.l4[1] * G(-1)) + T(27) * (rc.l4[2] * G(0)) -
+                   rc.l4[3] * G(1);
+  const T lap_ph = rc.lp4 * ((-mp(-2) + T(16) * mp(-1)) - T(30) * mp(0) + (T(16) * mp(1) - mp(2)));
+  Lphi = c.M * (lap_th + lap_ph);
+  if (c.ch_adv)
+    Lphi -= ((P(-2) - T(8) * P(-1)) + (T(8) * P(1) - P(2))) * rc.inv_12rJdth +
+            ((Q(-2) - T(8) * Q(-1)) + (T(8) * Q(1) - Q(2))) * rc.inv_12Jdph;
+}
+
+// Runge-Kutta combine of the order parameter: own = its stored value at the stage input (FP32: the
+// deviation from the base), yn = the one of y^n.
+template <typename T>
+__device__ __forceinline__ T phi_update(T own, T yn, T Lphi, T dt, T a0, T b1, bool y0) {
+  TLB_EXPLICIT_FMA
+  const T ys = fused(dt, Lphi, own);
+  if (!y0) return ys;
+  // FP32: a0 d^n + b1 (d_s + dt L) as d^n + b1 ((d_s - d^n) + dt L) (a0 + b1 = 1), on the
+  // deviations from the base, which are small where phi sits near +-1 in the bulk: there the
+  // increments are far below half an ulp of 1 and would be lost on phi itself
+  if constexpr (stores_deviation<T>()) return fused(b1, fused(dt, Lphi, own - yn), yn);
+  return products(a0, yn, b1, ys);
+}
+
+// Update of population (i, j) at a node: the equilibrium (eq. feq) as a cubic in xi = v.u,
+//   f_eq = n w_i w_j [c0 (1 + xi) + xi^2/2 + xi^3/6],  c0 = 1 - u^2/2,
+// and the velocity derivatives (section II C), (df/dv^theta)_ij = sum_m K_im f_mj,
+// (df/dv^phi)_ij = sum_m K_jm f_im, (d(f v^phi)/dv^phi)_ij = sum_m K_jm v_m f_im, so the force and
+// connection terms combine into
+//   S_ij = (G v_j^2 - F^theta) sum_m K_im f_mj - sum_m K_jm (F^phi + G v_i v_m) f_im.
+// dvt, dvp: the two sums over m of the stored populations; c_t = w_j sum_m K_im w_m and
+// c_p = v_i sum_m K_jm v_m w_m give those of the stored constant n_ref w_i w_j in closed form;
+// ct = G v_j^2 - F^theta (theta_factor).  Returns y_s + dt L.
+template <typename T>
+__device__ __forceinline__ T theta_factor(bool outer, T G, T vj2, T Xth, T inv_n) {
+  TLB_EXPLICIT_FMA
+  return outer ? fused(G, vj2, Xth * inv_n) : fused(Xth, inv_n, G * vj2);
+}
+template <typename T, bool GENREF>
+__device__ __forceinline__ T population_update(T f, T adv, T dvt, T dvp, T vi, T vj, T w_i, T ww,
+                                               T kw_j, T c_t, T c_p, T n, T dn, T n_ref, T ut,
+                                               T up, T u2, T c0, T G, T ct, T Fph, T inv_tau,
+                                               T dt) {
+  TLB_EXPLICIT_FMA
+  const T xi = products(vi, ut, vj, up);
+  T relax;  // f_eq - f, in the stored representation
+  if constexpr (stores_deviation<T>()) {
+    const T force = products(Fph, kw_j, G, c_p);
+    dvt = fused(n_ref, c_t, dvt);
+    dvp = GENREF ? fused(n_ref, w_i * force, dvp) : fused(w_i, force, dvp);
+    // f_eq - n_ref w_i w_j = w_i w_j (n_ref p1 + dn (1 + p1)), p1 = poly - 1, all small
+    const T p1 = fused(xi, fused(xi, fused(xi, T(1.0 / 6.0), T(0.5)), c0), T(-0.5) * u2);
+    const T x = GENREF ? products(n_ref, p1, dn, T(1) + p1) : fused(dn, T(1) + p1, p1);
+    relax = fused(ww, x, -f);
+  } else {
+    const T poly = fused(xi, fused(xi, fused(xi, T(1.0 / 6.0), T(0.5)), c0), c0);
+    relax = fused(n * ww, poly, -f);
+  }
+  const T L = fused(relax, inv_tau, fused(ct, dvt, adv) - dvp);
+  return fused(dt, L, f);
 }
 
 // Populations are consumed in groups of PB: one wait and one block barrier per group, after
@@ -632,51 +781,31 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
     const T* buf = slot(ic<k>{});
     f[k] = buf[cN];
     n += f[k];
-    nut += T(vel(i)) * f[k];
-    nup += T(vel(j)) * f[k];
+    nut = fused(T(vel(i)), f[k], nut);
+    nup = fused(T(vel(j)), f[k], nup);
     // phi direction: sum_o uw5(o) f_{s+o}, upwind side by the sign of v_j
     T dph, dth;
     if constexpr (WENO) {
       weno_advection<T, i, j, k>(buf + cN, Jnb, inv_rJdth, n_ref, dph, dth);
     } else {
-    if constexpr (j >= 2) {
-      dph = T(uw5p(-3)) * buf[cN - 3];
-      static_for<-2, 3>([&](auto oc) {
-        constexpr int o = decltype(oc)::value;
-        dph += T(uw5p(o)) * buf[cN + o];
-      });
-    } else {
-      dph = T(uw5m(-2)) * buf[cN - 2];
-      static_for<-1, 4>([&](auto oc) {
-        constexpr int o = decltype(oc)::value;
-        dph += T(uw5m(o)) * buf[cN + o];
-      });
-    }
+    dph = uw5_difference<T, j >= 2>([&](int o) { return buf[cN + o]; });
     // theta direction: sum_o uw5(o) J_{q+o} / (r J_q dtheta) f_{q+o}
-    if constexpr (i >= 2) {
-      dth = rc.bth_p[0] * buf[cN - 3 * LXT];
-      static_for<-2, 3>([&](auto oc) {
-        constexpr int o = decltype(oc)::value;
-        dth += rc.bth_p[o + 3] * buf[cN + o * LXT];
-      });
-    } else {
-      dth = rc.bth_m[0] * buf[cN - 2 * LXT];
-      static_for<-1, 4>([&](auto oc) {
-        constexpr int o = decltype(oc)::value;
-        dth += rc.bth_m[o + 2] * buf[cN + o * LXT];
-      });
+    constexpr int lo = i >= 2 ? -3 : -2;
+    auto bth = [&](int o) { return i >= 2 ? rc.bth_p[o] : rc.bth_m[o]; };
+    dth = products(bth(0), buf[cN + lo * LXT], bth(1), buf[cN + (lo + 1) * LXT]);
+    static_for<2, 6>([&](auto oc) {
+      constexpr int o = decltype(oc)::value;
+      dth = fused(bth(o), buf[cN + (lo + o) * LXT], dth);
+    });
     }
-    // deviation storage: the constant n_ref w_i w_j drops out of the phi differences (their
-    // weights sum to zero) but not out of the J-weighted theta differences
-    if constexpr (stores_deviation<T>())
-      dth += (n_ref * T(rest_offset<T>(k))) * (i >= 2 ? rc.bsum_p : rc.bsum_m);
-    }
-    adv[k] = T(-vel(i)) * dth + (T(-vel(j)) * inv_Jdph) * dph;
+    adv[k] = advection<T>(theta_first(i, j), fuse_constant(i, j), dth, dph, T(vel(i)),
+                          T(-vel(j)) * inv_Jdph, WENO ? T(0) : n_ref * T(rest_offset<T>(k)),
+                          i >= 2 ? rc.bsum_p : rc.bsum_m);
     if (ring) {
       const T fr = buf[cR];
       rn += fr;
-      rut += T(vel(i)) * fr;
-      rup += T(vel(j)) * fr;
+      rut = fused(T(vel(i)), fr, rut);
+      rup = fused(T(vel(j)), fr, rup);
     }
     // keep the arithmetic of this population here: without the pin the compiler sinks it to
     // the end of the kernel and holds every stencil value of all 16 populations live
@@ -730,114 +859,64 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
   __syncthreads();
 
   // ---- interface force n F = -phi grad mu and the Cahn-Hilliard right-hand side
-  T Fth, Fph, Lphi;
+  T Xth, Fph, Lphi;
   if constexpr (CH4) {
-    // fourth-order central grad mu, the fourth-order surface Laplacian of mu (staggered along
-    // theta: face gradients (m_{a-1} - 27 m_a + 27 m_{a+1} - m_{a+2}) at the faces a+1/2,
-    // a = q-2 .. q+1, weighted by J_face / (576 r^2 J dtheta^2) with (1, -27, 27, -1); the
-    // five-point fourth-order difference along phi) and fourth-order central flux differences
     const T* m = sMu4 + cN;
-    auto G = [&](int o) {  // face gradient numerator at the face (q + o) + 1/2
-      return m[(o - 1) * LXT] - T(27) * m[o * LXT] + T(27) * m[(o + 1) * LXT] - m[(o + 2) * LXT];
-    };
-    const T dmu_th = (m[-2 * LXT] - T(8) * m[-LXT]) + (T(8) * m[LXT] - m[2 * LXT]);
-    const T dmu_ph = (m[-2] - T(8) * m[-1]) + (T(8) * m[1] - m[2]);
-    Fth = -phc * dmu_th * a.c.inv_12rdth * inv_n;
-    Fph = -phc * dmu_ph * rc.inv_12Jdph * inv_n;
-    const T lap_th = rc.l4[0] * G(-2) - T(27) * (rc.l4[1] * G(-1)) + T(27) * (rc.l4[2] * G(0)) -
-                     rc.l4[3] * G(1);
-    const T lap_ph = rc.lp4 * ((-m[-2] + T(16) * m[-1]) - T(30) * m[0] + (T(16) * m[1] - m[2]));
-    Lphi = a.c.M * (lap_th + lap_ph);
-    if (a.c.ch_adv) {
-      const T* P = sP4 + cN;
-      const T* Q = sQ4 + cN;
-      Lphi -= ((P[-2 * LXT] - T(8) * P[-LXT]) + (T(8) * P[LXT] - P[2 * LXT])) * rc.inv_12rJdth +
-              ((Q[-2] - T(8) * Q[-1]) + (T(8) * Q[1] - Q[2])) * rc.inv_12Jdph;
-    }
+    const T* P = sP4 + cN;
+    const T* Q = sQ4 + cN;
+    ch4_rhs(phc, inv_n, rc, a.c, [&](int o) { return m[o * LXT]; }, [&](int o) { return m[o]; },
+            [&](int o) { return P[o * LXT]; }, [&](int o) { return Q[o]; }, Xth, Fph, Lphi);
   } else {
     const int cm = (ly + 1) * (TX + 2) + lx + 1;
-    const T mu_c = sMu[cm], mu_n = sMu[cm + TX + 2], mu_s = sMu[cm - (TX + 2)];
-    const T mu_e = sMu[cm + 1], mu_w = sMu[cm - 1];
-    Fth = -phc * (mu_n - mu_s) * a.c.inv_2rdth * inv_n;
-    Fph = -phc * (mu_e - mu_w) * rc.inv_2Jdph * inv_n;
-    const T lapmu = rc.lap_n * (mu_n - mu_c) - rc.lap_s * (mu_c - mu_s) +
-                    rc.lap_p * (mu_e - T(2) * mu_c + mu_w);
-    Lphi = a.c.M * lapmu;
-    if (a.c.ch_adv) {
-      const int ct = (ly + 1) * TX + lx, cp = ly * (TX + 2) + lx + 1;
-      Lphi -= (sPt[ct + TX] - sPt[ct - TX]) * rc.inv_2rJdth +
-              (sPp[cp + 1] - sPp[cp - 1]) * rc.inv_2Jdph;
-    }
+    const int ct = (ly + 1) * TX + lx, cp = ly * (TX + 2) + lx + 1;
+    ch_rhs(phc, inv_n, rc, a.c, sMu[cm], sMu[cm + TX + 2], sMu[cm - (TX + 2)], sMu[cm + 1],
+           sMu[cm - 1], sPt[ct + TX], sPt[ct - TX], sPp[cp + 1], sPp[cp - 1], Xth, Fph, Lphi);
   }
-
 
   const T dt = a.c.dt, a0 = a.a0, b1 = a.b1;
   const bool y0 = a.has_y0;
   if (active) {
     // the stored value at the node: FP32 the deviation from the base, FP64 phi itself
     const T own = stores_deviation<T>() ? dsn : phc;
-    const T ys = own + dt * Lphi;
     T yn0 = phin;
     if constexpr (!PF)
       if (y0) yn0 = *at_node(a.phi0, row0, lane_bytes);
-    T out = ys;
-    if constexpr (stores_deviation<T>()) {
-      // FP32: a0 d^n + b1 (d_s + dt L) as d^n + b1 ((d_s - d^n) + dt L) (a0 + b1 = 1), on the
-      // deviations from the base, which are small where phi sits near +-1 in the bulk: there
-      // the increments are far below half an ulp of 1 and would be lost on phi itself
-      if (y0) out = yn0 + b1 * ((own - yn0) + dt * Lphi);
-    } else {
-      if (y0) out = a0 * yn0 + b1 * ys;
-    }
+    const T out = phi_update(own, yn0, Lphi, dt, a0, b1, y0);
     put<STREAM>(at_node(a.phiout, row0, lane_bytes), out);
   }
 
-  // ---- equilibrium (eq. feq) as a cubic in xi = v.u:
-  //      f_eq = n w_i w_j [c0 (1 + xi) + xi^2/2 + xi^3/6],  c0 = 1 - u^2/2
-  // ---- velocity derivatives (section II C): (df/dv^theta)_ij = sum_m K_im f_mj,
-  //      (df/dv^phi)_ij = sum_m K_jm f_im, (d(f v^phi)/dv^phi)_ij = sum_m K_jm v_m f_im, so the
-  //      force and connection terms combine into
-  //      S_ij = (G v_j^2 - F^theta) sum_m K_im f_mj - sum_m K_jm (F^phi + G v_i v_m) f_im.
-  const T c0 = T(1) - T(0.5) * (ut * ut + up * up);
+  // ---- equilibrium, force and connection terms, Runge-Kutta combine
+  const T u2 = products(ut, ut, up, up);
+  const T c0 = fused(T(-0.5), u2, T(1));
   const T G = rc.G;
+  const T ct[2] = {theta_factor(false, G, T(VIN * VIN), Xth, inv_n),
+                   theta_factor(true, G, T(VOUT * VOUT), Xth, inv_n)};
   T g[16];
   static_for<0, 16>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
     constexpr int i = k >> 2, m = k & 3;
-    g[k] = (Fph + G * T(vel(i) * vel(m))) * f[k];
+    g[k] = fused(G, T(vel(i) * vel(m)), Fph) * f[k];
   });
   static_for<0, 16>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
     constexpr int i = k >> 2, j = k & 3;
-    T dvt = T(0), dvp = T(0);
-    static_for<0, 4>([&](auto mc) {
+    T dvt = T(kh(i, 0)) * f[j], dvp = T(kh(j, 0)) * g[4 * i];
+    static_for<1, 4>([&](auto mc) {
       constexpr int m = decltype(mc)::value;
-      dvt += T(kh(i, m)) * f[4 * m + j];
-      dvp += T(kh(j, m)) * g[4 * i + m];
+      dvt = fused(T(kh(i, m)), f[4 * m + j], dvt);
+      dvp = fused(T(kh(j, m)), g[4 * i + m], dvp);
     });
-    if constexpr (stores_deviation<T>()) {
-      // the velocity derivatives of the stored constant n_ref w_i w_j, in closed form
-      dvt += n_ref * T(wgt(j) * kw(i));
-      dvp += n_ref * (T(wgt(i)) * (Fph * T(kw(j)) + G * T(vel(i) * kvw(j))));
-    }
-    const T xi = T(vel(i)) * ut + T(vel(j)) * up;
-    T relax;  // f_eq - f, in the stored representation
-    if constexpr (stores_deviation<T>()) {
-      // f_eq - n_ref w_i w_j = w_i w_j (n_ref p1 + dn (1 + p1)), p1 = poly - 1, all small
-      const T p1 = T(-0.5) * (ut * ut + up * up) + xi * (c0 + xi * (T(0.5) + xi * T(1.0 / 6.0)));
-      relax = T(wgt(i) * wgt(j)) * (n_ref * p1 + dn * (T(1) + p1)) - f[k];
-    } else {
-      const T poly = c0 + xi * (c0 + xi * (T(0.5) + xi * T(1.0 / 6.0)));
-      relax = (n * T(wgt(i) * wgt(j))) * poly - f[k];
-    }
-    const T L = adv[k] + (G * T(vel(j) * vel(j)) - Fth) * dvt - dvp + relax * a.c.inv_tau;
-    const T ys = f[k] + dt * L;
+    const T ys = population_update<T, GENREF>(
+        f[k], adv[k], dvt, dvp, T(vel(i)), T(vel(j)), T(wgt(i)), T(wgt(i) * wgt(j)), T(kw(j)),
+        T(wgt(j) * kw(i)), T(vel(i) * kvw(j)), n, dn, n_ref, ut, up, u2, c0, G,
+        ct[(j == 0 || j == 3) ? 1 : 0], Fph, a.c.inv_tau, dt);
     if (active) {
       T* dst = at_node(a.fout, k * a.plane + row0, lane_bytes);
       if constexpr (PF)
-        put<STREAM>(dst, y0 ? a0 * yn[k] + b1 * ys : ys);
+        put<STREAM>(dst, y0 ? products(a0, yn[k], b1, ys) : ys);
       else
-        put<STREAM>(dst, y0 ? a0 * *at_node(a.f0, k * a.plane + row0, lane_bytes) + b1 * ys : ys);
+        put<STREAM>(dst, y0 ? products(a0, *at_node(a.f0, k * a.plane + row0, lane_bytes), b1, ys)
+                            : ys);
     }
   });
 #endif
@@ -866,47 +945,320 @@ __global__ __launch_bounds__(Tile<TY>::NT) __attribute__((amdgpu_waves_per_eu(
   stage_tile<T, VEC, TY, WENO, STREAM, GENREF, CH4>(a, tx, ty);
 }
 
-// The fourth-order surface Laplacian (TLB_CH4) of a plane h at node (q, s), read from global
-// memory: staggered along theta (face gradient numerators h_{a-1} - 27 h_a + 27 h_{a+1} -
+// The fourth-order surface Laplacian (TLB_CH4) from the values c at rows q-3 .. q+3 and h at columns
+// s-2 .. s+2: staggered along theta (face gradient numerators h_{a-1} - 27 h_a + 27 h_{a+1} -
 // h_{a+2} at the faces a+1/2, a = q-2 .. q+1, weighted by rc.l4 with (1, -27, 27, -1)), the
 // five-point fourth-order difference along phi.
 template <typename T>
-__device__ __forceinline__ T lap4_at(const T* h, const T* hb, const RowCoef<T>& rc, int q,
-                                     int s, int nt, int np) {
-  T c[7];  // rows q-3 .. q+3 of column s
-#pragma unroll
-  for (int o = -3; o <= 3; ++o) c[o + 3] = phi_val(h, hb, (long long)wrapi(q + o, nt) * np + s);
+__device__ __forceinline__ T lap4_of(const T (&c)[7], const T (&h)[5], const RowCoef<T>& rc) {
   auto G = [&](int o) { return c[o + 2] - T(27) * c[o + 3] + T(27) * c[o + 4] - c[o + 5]; };
-  const long long row = (long long)q * np;
-  const T e1 = phi_val(h, hb, row + wrapi(s + 1, np)), e2 = phi_val(h, hb, row + wrapi(s + 2, np));
-  const T w1 = phi_val(h, hb, row + wrapi(s - 1, np)), w2 = phi_val(h, hb, row + wrapi(s - 2, np));
   const T lap_th = rc.l4[0] * G(-2) - T(27) * (rc.l4[1] * G(-1)) + T(27) * (rc.l4[2] * G(0)) -
                    rc.l4[3] * G(1);
-  const T lap_ph = rc.lp4 * ((-w2 + T(16) * w1) - T(30) * c[3] + (T(16) * e1 - e2));
+  const T lap_ph = rc.lp4 * ((-h[0] + T(16) * h[1]) - T(30) * c[3] + (T(16) * h[3] - h[4]));
   return lap_th + lap_ph;
 }
-
-// TLB_CH4 prepass, one thread per node (see Ch4Args)
+// ... of a plane at node (q, s), read from global memory
 template <typename T>
-__global__ __launch_bounds__(256) void tlb_ch4_prep_kernel(Ch4Args<T> a) {
-  const long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= a.plane) return;
-  const int q = (int)(x / a.np), s = (int)(x - (long long)q * a.np);
+__device__ __forceinline__ T lap4_at(const T* h, const T* hb, const RowCoef<T>& rc, int q,
+                                     int s, int nt, int np) {
+  T c[7], w[5];
+#pragma unroll
+  for (int o = -3; o <= 3; ++o) c[o + 3] = phi_val(h, hb, (long long)wrapi(q + o, nt) * np + s);
+#pragma unroll
+  for (int o = -2; o <= 2; ++o) w[o + 2] = phi_val(h, hb, (long long)q * np + wrapi(s + o, np));
+  return lap4_of(c, w, rc);
+}
+
+// TLB_CH4 prepass (see Ch4Args): one wavefront per 64-node row segment, so that rows are scalars,
+// the periodic neighbours come one step at a time without divisions, and small grids still have
+// many workgroups.
+template <typename T>
+__global__ __launch_bounds__(64) void tlb_ch4_prep_kernel(Ch4Args<T> a) {
+  const int nt = a.nt, np = a.np;
+  const int q = blockIdx.x / a.ntx, s = (blockIdx.x - q * a.ntx) * TX + threadIdx.x;
+  if (s >= np) return;
+  long long row[7];
+  unsigned col[5];
+  {
+    int r[7], c[5];
+    r[3] = q;
+    c[2] = s;
+#pragma unroll
+    for (int o = 1; o <= 3; ++o) {
+      r[3 - o] = r[4 - o] == 0 ? nt - 1 : r[4 - o] - 1;
+      r[3 + o] = r[2 + o] + 1 == nt ? 0 : r[2 + o] + 1;
+    }
+#pragma unroll
+    for (int o = 1; o <= 2; ++o) {
+      c[2 - o] = c[3 - o] == 0 ? np - 1 : c[3 - o] - 1;
+      c[2 + o] = c[1 + o] + 1 == np ? 0 : c[1 + o] + 1;
+    }
+#pragma unroll
+    for (int o = 0; o < 7; ++o) row[o] = (long long)r[o] * np;
+#pragma unroll
+    for (int o = 0; o < 5; ++o) col[o] = (unsigned)c[o] * (unsigned)sizeof(T);
+  }
+  auto phi_at = [&](long long r, unsigned c) {
+    T v = *at_node(a.phi, r, c);
+    if constexpr (stores_deviation<T>()) v = v + *at_node(a.phib, r, c);
+    return v;
+  };
+  T c[7], h[5];  // phi at rows q - 3 .. q + 3 and columns s - 2 .. s + 2
+#pragma unroll
+  for (int o = 0; o < 7; ++o) c[o] = phi_at(row[o], col[2]);
+#pragma unroll
+  for (int o = 0; o < 5; ++o) h[o] = phi_at(row[3], col[o]);
+  T f[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) f[k] = *at_node(a.f, k * a.plane + row[3], col[2]);
   T n = T(0), nut = T(0), nup = T(0);
   static_for<0, 16>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
-    const T fk = a.f[k * a.plane + x];
-    n += fk;
-    nut += T(vel(k >> 2)) * fk;
-    nup += T(vel(k & 3)) * fk;
+    n += f[k];
+    nut += T(vel(k >> 2)) * f[k];
+    nup += T(vel(k & 3)) * f[k];
   });
   if constexpr (stores_deviation<T>()) n += a.n_ref;
   const T inv_n = recip(n);
   const RowCoef<T> rc = a.rows[q];
-  const T ph = phi_val(a.phi, a.phib, x);
-  a.mu[x] = a.A * ph * (ph * ph - T(1)) - a.kappa * lap4_at(a.phi, a.phib, rc, q, s, a.nt, a.np);
-  a.P[x] = rc.J * (nut * inv_n) * ph;
-  a.Q[x] = (nup * inv_n) * ph;
+  const T ph = c[3];
+  *at_node(a.mu, row[3], col[2]) = a.A * ph * (ph * ph - T(1)) - a.kappa * lap4_of(c, h, rc);
+  *at_node(a.P, row[3], col[2]) = rc.J * (nut * inv_n) * ph;
+  *at_node(a.Q, row[3], col[2]) = (nup * inv_n) * ph;
+}
+
+// ------------------------------------------------------------------------------------------
+// Runge-Kutta stage of a small grid: the arithmetic of stage_tile, node by node, with a wavefront
+// per 64-node row segment and velocity v_i (four per block).  A grid of few tiles leaves most of
+// the chip idle while each tile's block walks through its sixteen populations; here a wavefront has
+// four of them, reads their stencils straight from the caches in one go (no halo tile, no ring)
+// and meets the others at one barrier, where the populations of the node and the neighbours'
+// chemical potential and Cahn-Hilliard fluxes (wavefront i computes neighbour i's) are exchanged.
+// Bound by the launch and one chain of load, exchange and store latencies.
+// 64 x 160 (192 segments): 4.0 us per stage in FP32 and 5.6 in FP64, of which 1.8 are the launch;
+// the tile kernel took 7.5 and 10.0.
+//
+// The four wavefronts run the same instructions (v_i and its coefficients are wavefront-uniform
+// values, not compile-time constants), so that they share their instruction fetches.
+template <typename T>
+struct VelocityTables {  // rounded once from FP64, as the constants of stage_tile are
+  T kh[4][4];            // K^H_im
+  T vv[4][4];            // v_i v_m
+  T ww[4][4];            // w_i w_j
+  T wkw[4][4];           // w_j sum_m K^H_im w_m
+  T vkvw[4][4];          // v_i sum_m K^H_jm v_m w_m
+  T rest[4][4];          // rest_offset
+  T v[4], w[4], kw[4];
+};
+template <typename T>
+constexpr VelocityTables<T> make_velocity_tables() {
+  VelocityTables<T> t{};
+  for (int i = 0; i < 4; ++i) {
+    for (int j = 0; j < 4; ++j) {
+      t.kh[i][j] = T(kh(i, j));
+      t.vv[i][j] = T(vel(i) * vel(j));
+      t.ww[i][j] = T(wgt(i) * wgt(j));
+      t.wkw[i][j] = T(wgt(j) * kw(i));
+      t.vkvw[i][j] = T(vel(i) * kvw(j));
+      t.rest[i][j] = T(rest_offset<T>(4 * i + j));
+    }
+    t.v[i] = T(vel(i));
+    t.w[i] = T(wgt(i));
+    t.kw[i] = T(kw(i));
+  }
+  return t;
+}
+template <typename T>
+__constant__ constexpr VelocityTables<T> velocity_tables = make_velocity_tables<T>();
+
+template <typename T, bool GENREF, bool CH4>
+__global__ __launch_bounds__(256) void tlb_stage_small_kernel(StageArgs<T> a) {
+  __shared__ T sF[16][TX], sMuN[4][TX], sFlux[4][TX];
+  const int lane = threadIdx.x & 63;
+  const int i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // this wavefront's v_i
+  const int nt = a.nt, np = a.np;
+  const int t = xcd_tile(blockIdx.x, nt * a.ntx);
+  const int q = t / a.ntx, s = (t - q * a.ntx) * TX + lane;
+  const bool active = s < np;
+  const VelocityTables<T>* const vt = &velocity_tables<T>;
+  // Columns s - 3 .. s + 3 as byte offsets in a row, and the starts of rows q - 3 .. q + 3 (scalars),
+  // one periodic step at a time, which is right for any length; lanes past the row's end read its
+  // last node.  Every load below takes a scalar base and one of these offsets, and no branch comes
+  // before it: the first is issued after some 100 instructions (with a general wrap of every
+  // index it was 900, half of the kernel's time).
+  unsigned col[7];
+  long long row[7];
+  {
+    int c[7], r[7];
+    c[3] = min(s, np - 1);
+    r[3] = q;
+#pragma unroll
+    for (int o = 1; o <= 3; ++o) {
+      c[3 - o] = c[4 - o] == 0 ? np - 1 : c[4 - o] - 1;
+      c[3 + o] = c[2 + o] + 1 == np ? 0 : c[2 + o] + 1;
+      r[3 - o] = r[4 - o] == 0 ? nt - 1 : r[4 - o] - 1;
+      r[3 + o] = r[2 + o] + 1 == nt ? 0 : r[2 + o] + 1;
+    }
+#pragma unroll
+    for (int o = 0; o < 7; ++o) {
+      col[o] = (unsigned)c[o] * (unsigned)sizeof(T);
+      row[o] = (long long)r[o] * np;
+    }
+  }
+  T n_ref = T(1);
+  if constexpr (GENREF) n_ref = a.c.n_ref;
+
+  // ---- loads: the stencils of populations 4 i .. 4 i + 3, y^n (loaded but not used in
+  //      stage 1), and what this wavefront contributes to the exchange
+  const bool up_i = i >= 2;
+  T th[4][6], ph[4][7], yn[4];
+  long long trow[6];  // theta stencil: rows q - 3 .. q + 2 (v_i > 0) or q - 2 .. q + 3
+#pragma unroll
+  for (int o = 0; o < 6; ++o) trow[o] = up_i ? row[o] : row[o + 1];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const long long pl = (4 * i + j) * a.plane;
+#pragma unroll
+    for (int o = 0; o < 6; ++o) th[j][o] = *at_node(a.fin, pl + trow[o], col[3]);
+#pragma unroll
+    for (int o = 0; o < 7; ++o)
+      if (o != 3 && o >= (j >= 2 ? 0 : 1) && o <= (j >= 2 ? 5 : 6))
+        ph[j][o] = *at_node(a.fin, pl + row[3], col[o]);
+  }
+  auto phi_at = [&](long long r, unsigned c) {
+    T v = *at_node(a.phin, r, c);
+    if constexpr (stores_deviation<T>()) v = *at_node(a.phib, r, c) + v;
+    return v;
+  };
+  const T own = *at_node(a.phin, row[3], col[3]);
+  T phc = own;
+  if constexpr (stores_deviation<T>()) phc = *at_node(a.phib, row[3], col[3]) + own;
+  T nb[CH4 ? 1 : 16], pb[9];
+  // neighbour i: 0 north, 1 south, 2 east, 3 west
+  const int dq = i == 0 ? 1 : i == 1 ? -1 : 0, ds = i == 2 ? 1 : i == 3 ? -1 : 0;
+  if constexpr (!CH4) {
+    auto pick = [](int d, auto plus, auto zero, auto minus) {
+      return d > 0 ? plus : d < 0 ? minus : zero;
+    };
+    const long long rw = pick(dq, row[4], row[3], row[2]), rwp = pick(dq, row[5], row[4], row[3]),
+                    rwm = pick(dq, row[3], row[2], row[1]);
+    const unsigned cl = pick(ds, col[4], col[3], col[2]), clp = pick(ds, col[5], col[4], col[3]),
+                   clm = pick(ds, col[3], col[2], col[1]);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) nb[k] = *at_node(a.fin, k * a.plane + rw, cl);
+    pb[0] = phi_at(rw, cl);
+    pb[1] = phi_at(rwp, cl);
+    pb[2] = phi_at(rwm, cl);
+    pb[3] = phi_at(rw, clp);
+    pb[4] = phi_at(rw, clm);
+    pb[5] = phi_at(row[4], col[3]);
+    pb[6] = phi_at(row[2], col[3]);
+    pb[7] = phi_at(row[3], col[4]);
+    pb[8] = phi_at(row[3], col[2]);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) yn[j] = *at_node(a.f0, (4 * i + j) * a.plane + row[3], col[3]);
+  const T yn0 = *at_node(a.phi0, row[3], col[3]);
+
+  const RowCoef<T> rc = a.rows[q];
+  T mu_c = T(0);
+  if constexpr (!CH4) {
+    const RowCoef<T>& rrc = a.rows[dq > 0 ? (q + 1 == nt ? 0 : q + 1)
+                                   : dq < 0 ? (q == 0 ? nt - 1 : q - 1) : q];
+    mu_c = mu_of(phc, pb[5], pb[6], pb[7], pb[8], rc, a.c.A, a.c.kappa);
+    T rn = T(0), rut = T(0), rup = T(0);
+    static_for<0, 16>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
+      rn += nb[k];
+      rut = fused(T(vel(k >> 2)), nb[k], rut);
+      rup = fused(T(vel(k & 3)), nb[k], rup);
+    });
+    if constexpr (stores_deviation<T>()) rn += n_ref;
+    const T inv_rn = recip(rn);
+    sMuN[i][lane] = mu_of(pb[0], pb[1], pb[2], pb[3], pb[4], rrc, a.c.A, a.c.kappa);
+    sFlux[i][lane] = i < 2 ? rrc.J * (rut * inv_rn) * pb[0] : (rup * inv_rn) * pb[0];
+  }
+
+  // ---- advection of the wavefront's populations (as in stage_tile)
+  T bth[6];
+#pragma unroll
+  for (int o = 0; o < 6; ++o) bth[o] = up_i ? rc.bth_p[o] : rc.bth_m[o];
+  const T vi = vt->v[i], inv_Jdph = rc.inv_Jdph;
+  T fo[4], adv[4];
+  static_for<0, 4>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    fo[j] = up_i ? th[j][3] : th[j][2];
+    sF[4 * i + j][lane] = fo[j];
+    T dph, dth;
+    dph = uw5_difference<T, j >= 2>([&](int o) { return o == 0 ? fo[j] : ph[j][o + 3]; });
+    dth = products(bth[0], th[j][0], bth[1], th[j][1]);
+#pragma unroll
+    for (int o = 2; o < 6; ++o) dth = fused(bth[o], th[j][o], dth);
+    adv[j] = advection<T>(theta_first(i, j), fuse_constant(i, j), dth, dph, vi,
+                          T(-vel(j)) * inv_Jdph, n_ref * vt->rest[i][j],
+                          up_i ? rc.bsum_p : rc.bsum_m);
+  });
+  __syncthreads();
+
+  // ---- moments of the node, force and Cahn-Hilliard right-hand side
+  T f[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) f[k] = sF[k][lane];
+  T n = T(0), nut = T(0), nup = T(0);
+  static_for<0, 16>([&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    n += f[k];
+    nut = fused(T(vel(k >> 2)), f[k], nut);
+    nup = fused(T(vel(k & 3)), f[k], nup);
+  });
+  const T dn = n;
+  if constexpr (stores_deviation<T>()) n += n_ref;
+  const T inv_n = recip(n);
+  const T ut = nut * inv_n, up = nup * inv_n;
+  T Xth, Fph, Lphi;
+  if constexpr (CH4) {
+    T mth[7], mph[7];
+#pragma unroll
+    for (int o = 0; o < 7; ++o) {
+      mth[o] = *at_node(a.mu4, row[o], col[3]);
+      mph[o] = *at_node(a.mu4, row[3], col[o]);
+    }
+    ch4_rhs(phc, inv_n, rc, a.c, [&](int o) { return mth[o + 3]; },
+            [&](int o) { return mph[o + 3]; },
+            [&](int o) { return *at_node(a.P4, row[o + 3], col[3]); },
+            [&](int o) { return *at_node(a.Q4, row[3], col[o + 3]); }, Xth, Fph, Lphi);
+  } else {
+    ch_rhs(phc, inv_n, rc, a.c, mu_c, sMuN[0][lane], sMuN[1][lane], sMuN[2][lane], sMuN[3][lane],
+           sFlux[0][lane], sFlux[1][lane], sFlux[2][lane], sFlux[3][lane], Xth, Fph, Lphi);
+  }
+  if (!active) return;
+  const T dt = a.c.dt, a0 = a.a0, b1 = a.b1;
+  const bool y0 = a.has_y0;
+  if (i == 0) *at_node(a.phiout, row[3], col[3]) = phi_update(own, yn0, Lphi, dt, a0, b1, y0);
+
+  // ---- the populations' update (as in stage_tile)
+  const T u2 = products(ut, ut, up, up);
+  const T c0 = fused(T(-0.5), u2, T(1));
+  const T G = rc.G;
+  const T ct[2] = {theta_factor(false, G, T(VIN * VIN), Xth, inv_n),
+                   theta_factor(true, G, T(VOUT * VOUT), Xth, inv_n)};
+  T g[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) g[m] = fused(G, vt->vv[i][m], Fph) * fo[m];
+  static_for<0, 4>([&](auto jc) {
+    constexpr int j = decltype(jc)::value;
+    T dvt = vt->kh[i][0] * f[j], dvp = T(kh(j, 0)) * g[0];
+    static_for<1, 4>([&](auto mc) {
+      constexpr int m = decltype(mc)::value;
+      dvt = fused(vt->kh[i][m], f[4 * m + j], dvt);
+      dvp = fused(T(kh(j, m)), g[m], dvp);
+    });
+    const T ys = population_update<T, GENREF>(
+        fo[j], adv[j], dvt, dvp, vi, T(vel(j)), vt->w[i], vt->ww[i][j], T(kw(j)), vt->wkw[i][j],
+        vt->vkvw[i][j], n, dn, n_ref, ut, up, u2, c0, G, ct[(j == 0 || j == 3) ? 1 : 0], Fph,
+        a.c.inv_tau, dt);
+    *at_node(a.fout, (4 * i + j) * a.plane + row[3], col[3]) = y0 ? products(a0, yn[j], b1, ys) : ys;
+  });
 }
 
 // One stage for an ensemble of grids in one launch, one block per tile.  table[3 g + stage - 1]
@@ -1652,6 +2004,29 @@ bool streaming(const tlb_grid* g) {
   return 51.0 * g->p.n_theta * (double)g->p.n_phi * (double)g->elem > STREAMING_BYTES;
 }
 
+// The small-grid kernel runs grids of at most this many 64-node row segments (not WENO-5, whose
+// arithmetic outweighs the latencies).  Times per step in us, tiles / small-grid kernel: FP32, 960
+// segments 24.1 / 19.0, 1285 24.4 / 22.9, 1800 28.3 / 30.9; FP64, 320 segments 31.7 / 24.1, 640
+// 31.7 / 30.8, 960 33.8 / 38.1.
+constexpr long long small_rows(size_t elem) { return elem == 4 ? 1280 : 640; }
+
+long long row_segments(const tlb_grid* g) {
+  return (long long)g->p.n_theta * ((g->p.n_phi + TX - 1) / TX);
+}
+bool small_grid(const tlb_grid* g) {
+  return row_segments(g) <= small_rows(g->elem) && !(g->p.flags & TLB_WENO5);
+}
+
+template <typename T>
+const void* small_fn(const tlb_grid* g) {
+  const bool gen = general_reference<T>(g);
+  if (g->p.flags & TLB_CH4)
+    return gen ? reinterpret_cast<const void*>(&tlb_stage_small_kernel<T, true, true>)
+               : reinterpret_cast<const void*>(&tlb_stage_small_kernel<T, false, true>);
+  return gen ? reinterpret_cast<const void*>(&tlb_stage_small_kernel<T, true, false>)
+             : reinterpret_cast<const void*>(&tlb_stage_small_kernel<T, false, false>);
+}
+
 template <typename T>
 const void* stage_fn(const tlb_grid* g) {
   const bool vec = vec_ok<T>(g->p.n_phi), gen = general_reference<T>(g);
@@ -1731,19 +2106,26 @@ int stage_launches(const tlb_grid* g, int stage, tlbi_launch out[2]) {
     c.rows = a.rows;
     c.nt = a.nt;
     c.np = a.np;
+    c.ntx = a.ntx;
     c.plane = a.plane;
     c.A = T(g->p.A);
     c.kappa = T(g->p.kappa);
     c.n_ref = T(g->n_ref);
     out[n].fn = reinterpret_cast<const void*>(&tlb_ch4_prep_kernel<T>);
-    out[n].grid = dim3((unsigned)((a.plane + 255) / 256));
-    out[n].block = dim3(256);
+    out[n].grid = dim3((unsigned)row_segments(g));
+    out[n].block = dim3(TX);
     std::memcpy(out[n].args, &c, sizeof(c));
     ++n;
   }
-  out[n].fn = stage_fn<T>(g);
-  out[n].grid = dim3(stage_blocks(g));
-  out[n].block = dim3(TX * g->ty);
+  if (small_grid(g)) {
+    out[n].fn = small_fn<T>(g);
+    out[n].grid = dim3((unsigned)row_segments(g));
+    out[n].block = dim3(256);
+  } else {
+    out[n].fn = stage_fn<T>(g);
+    out[n].grid = dim3(stage_blocks(g));
+    out[n].block = dim3(TX * g->ty);
+  }
   std::memcpy(out[n].args, &a, sizeof(a));
   return n + 1;
 }
@@ -2735,7 +3117,7 @@ int32_t tlb_set_tile_rows(tlb_grid* g, int32_t rows) {
 int32_t tlb_autotune(tlb_grid* g, int32_t* rows) {
   clear_error();
   if (!g) return fail(TLB_EINVAL, "grid is NULL");
-  if (g->p.flags & (TLB_WENO5 | TLB_CH4)) {  // one tile height only
+  if ((g->p.flags & (TLB_WENO5 | TLB_CH4)) || small_grid(g)) {  // one tile height only, or no tiles
     if (rows) *rows = g->ty;
     return TLB_OK;
   }
