@@ -185,40 +185,46 @@ __host__ __device__ constexpr bool fuse_constant(int i, int j) {
 // On smooth data the weights tend to d and the face value to the UW5 one.
 constexpr double WENO_EPS = 1e-6;
 
+// Written in differences: with t the first and d the second differences, the candidates are
+// q1 = h0 + (t0 + 2 t1)/6, q0 = q1 + (d0 - d1)/3 and q2 = q1 + (d1 - d2)/6, so that the weights
+// (here times 4^-2, which cancels) only scale small terms: FP32 takes the hardware reciprocal for
+// them, FP64 one division for all three.
 template <typename T>
 __device__ __forceinline__ T weno5(T hm2, T hm1, T h0, T hp1, T hp2) {
-  const T q0 = (T(2) * hm2 - T(7) * hm1 + T(11) * h0) * T(1.0 / 6.0);
-  const T q1 = (T(5) * h0 - hm1 + T(2) * hp1) * T(1.0 / 6.0);
-  const T q2 = (T(2) * h0 + T(5) * hp1 - hp2) * T(1.0 / 6.0);
-  const T d0 = hm2 - T(2) * hm1 + h0, e0 = hm2 - T(4) * hm1 + T(3) * h0;
-  const T d1 = hm1 - T(2) * h0 + hp1, e1 = hm1 - hp1;
-  const T d2 = h0 - T(2) * hp1 + hp2, e2 = T(3) * h0 - T(4) * hp1 + hp2;
-  const T b0 = T(WENO_EPS) + T(13.0 / 12.0) * d0 * d0 + T(0.25) * e0 * e0;
-  const T b1 = T(WENO_EPS) + T(13.0 / 12.0) * d1 * d1 + T(0.25) * e1 * e1;
-  const T b2 = T(WENO_EPS) + T(13.0 / 12.0) * d2 * d2 + T(0.25) * e2 * e2;
-  const T a0 = T(0.1) / (b0 * b0), a1 = T(0.6) / (b1 * b1), a2 = T(0.3) / (b2 * b2);
-  return (a0 * q0 + a1 * q1 + a2 * q2) / (a0 + a1 + a2);
+  const T ta = hm1 - hm2, t0 = h0 - hm1, t1 = hp1 - h0, tb = hp2 - hp1;
+  const T d0 = t0 - ta, d1 = t1 - t0, d2 = tb - t1;
+  const T e0 = T(2) * t0 + d0, e1 = t0 + t1, e2 = T(2) * t1 - d2;
+  const T b0 = e0 * e0 + ((T(13.0 / 3.0) * d0) * d0 + T(4.0 * WENO_EPS));
+  const T b1 = e1 * e1 + ((T(13.0 / 3.0) * d1) * d1 + T(4.0 * WENO_EPS));
+  const T b2 = e2 * e2 + ((T(13.0 / 3.0) * d2) * d2 + T(4.0 * WENO_EPS));
+  T s0, s1, s2;  // proportional to 1 / b^2
+  if constexpr (std::is_same<T, float>::value) {
+    const T r0 = __builtin_amdgcn_rcpf(b0), r1 = __builtin_amdgcn_rcpf(b1),
+            r2 = __builtin_amdgcn_rcpf(b2);
+    s0 = r0 * r0;
+    s1 = r1 * r1;
+    s2 = r2 * r2;
+  } else {
+    const T p0 = b1 * b2, p1 = b0 * b2, p2 = b0 * b1;
+    s0 = p0 * p0;
+    s1 = p1 * p1;
+    s2 = p2 * p2;
+  }
+  // (0.1 s0 q0 + 0.6 s1 q1 + 0.3 s2 q2) / (0.1 s0 + 0.6 s1 + 0.3 s2)
+  const T sum = T(3) * s2 + (T(6) * s1 + s0);
+  const T num = T(1.5) * (s2 * (d1 - d2)) + s0 * (d0 - d1);
+  T q;
+  if constexpr (std::is_same<T, float>::value) q = num * __builtin_amdgcn_rcpf(sum);
+  else q = num / sum;
+  return h0 + (T(1.0 / 6.0) * (T(2) * t1 + t0) + T(1.0 / 3.0) * q);
 }
 
-// The two WENO-5 flux differences of population k = 4 i + j at a node: b points at the node in
-// the LDS population tile (rows LXT apart), Jnb holds J of the rows q-3..q+3.  Along phi the
-// stored values are used as they are (the reconstruction is shift-invariant, so deviations
-// give the same differences); along theta the flux h = J f of the full population.
-template <typename T, int I, int J, int K>
-__device__ __forceinline__ void weno_advection(const T* b, const T (&Jnb)[7], T inv_rJdth,
-                                               T n_ref, T& dph, T& dth) {
-  if constexpr (J >= 2)
-    dph = weno5(b[-2], b[-1], b[0], b[1], b[2]) - weno5(b[-3], b[-2], b[-1], b[0], b[1]);
-  else
-    dph = weno5(b[3], b[2], b[1], b[0], b[-1]) - weno5(b[2], b[1], b[0], b[-1], b[-2]);
-  T h[7];
-#pragma unroll
-  for (int o = 0; o < 7; ++o) h[o] = Jnb[o] * (b[(o - 3) * LXT] + n_ref * T(rest_offset<T>(K)));
-  if constexpr (I >= 2)
-    dth = weno5(h[1], h[2], h[3], h[4], h[5]) - weno5(h[0], h[1], h[2], h[3], h[4]);
-  else
-    dth = weno5(h[6], h[5], h[4], h[3], h[2]) - weno5(h[5], h[4], h[3], h[2], h[1]);
-  dth *= inv_rJdth;
+// The WENO-5 face value at +1/2 of the node that f(0) is, from the upwind side of v > 0 (POS) or
+// v < 0.
+template <typename T, bool POS, class F>
+__device__ __forceinline__ T weno_face(F f) {
+  if constexpr (POS) return weno5<T>(f(-2), f(-1), f(0), f(1), f(2));
+  else return weno5<T>(f(3), f(2), f(1), f(0), f(-1));
 }
 
 // Per theta-row coefficients (one record per row q), all derived on the host in FP64.
@@ -667,6 +673,11 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
   __shared__ T sPhiB[stores_deviation<T>() ? PY * LXT : 1];  // FP32: base tile, then phi itself
   // TLB_CH4: mu, J u^theta phi and u^phi phi of the prepass, halo tiles like the populations
   __shared__ T sMu4[CH4 ? TILE_SLOTS : 1], sP4[CH4 ? TILE_SLOTS : 1], sQ4[CH4 ? TILE_SLOTS : 1];
+  // WENO: the face values of two groups of populations in turn, along phi (column 0: the tile's
+  // left edge) and theta (row 0: its lower edge)
+  constexpr int PBW = Ring<T>::PB;
+  __shared__ T sFaceP[WENO ? 2 : 1][WENO ? PBW : 1][WENO ? TY * (TX + 1) : 1];
+  __shared__ T sFaceT[WENO ? 2 : 1][WENO ? PBW : 1][WENO ? (TY + 1) * TX : 1];
   __shared__ T sMu[(TY + 2) * (TX + 2)];
   __shared__ T sPt[(TY + 2) * TX];  // J u^theta phi on the tile and the rows above/below
   __shared__ T sPp[TY * (TX + 2)];  // u^phi phi on the tile and the columns left/right
@@ -740,14 +751,31 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
   const T inv_Jdph = rc.inv_Jdph;
   T n_ref = T(1);
   if constexpr (GENREF) n_ref = a.c.n_ref;
-  // WENO: J of rows q-3..q+3 (wavefront-uniform scalar loads) and 1 / (r J dtheta)
-  T Jnb[7];
+  // WENO: every face is reconstructed once and its value shared through LDS by the nodes on its two
+  // sides, so a population takes two reconstructions per node instead of four; the tile's left and
+  // lower edges are done beside them by wavefronts 0 .. 2 PB - 1.  The differences of a group of
+  // populations are taken after the next group's barrier, which its faces have then passed.  Along
+  // phi the stored values are used as they are (the reconstruction is shift-invariant), along theta
+  // the flux J f of the full population.  J of rows q-2..q+3 and of q0-3..q0+2 (scalar loads).
+  T Jnb[6], Jedge[6], face_p[PBW], face_t[PBW];
   T inv_rJdth = T(0);
   if constexpr (WENO) {
+    static_assert(TY >= 2 * PBW, "a wavefront for each edge and population of a group");
 #pragma unroll
-    for (int o = 0; o < 7; ++o) Jnb[o] = a.rows[wrapi(qw + o - 3, nt)].J;
+    for (int o = 0; o < 6; ++o) {
+      Jnb[o] = a.rows[wrapi(qw + o - 2, nt)].J;
+      Jedge[o] = a.rows[wrapi(q0 + o - 3, nt)].J;
+    }
     inv_rJdth = T(2) * rc.inv_2rJdth;
   }
+  auto weno_finish = [&](auto kc) {  // the differences of population k from the faces
+    constexpr int k = decltype(kc)::value;
+    constexpr int i = k >> 2, j = k & 3, h = (k / PBW) & 1, p = k % PBW;
+    const T dph = face_p[p] - sFaceP[WENO ? h : 0][WENO ? p : 0][WENO ? ly * (TX + 1) + lx : 0];
+    const T dth = (face_t[p] - sFaceT[WENO ? h : 0][WENO ? p : 0][WENO ? ly * TX + lx : 0]) * inv_rJdth;
+    adv[k] = advection<T>(false, false, dth, dph, T(vel(i)), T(-vel(j)) * inv_Jdph, T(0), T(0));
+    pin_reg(adv[k]);
+  };
 
   static_for<0, 16>([&](auto kc) {
     constexpr int k = decltype(kc)::value;
@@ -764,7 +792,9 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
       } else {
         wait_vm_lgkm0<ops_after_copy<D, DW, false, PB>(m, k)>();
       }
+      if constexpr (WENO) asm volatile("" ::: "memory");  // the face values stay on their side
       __builtin_amdgcn_s_barrier();
+      if constexpr (WENO) asm volatile("" ::: "memory");
       // every wave is past populations k-PB .. k-1: their ring slots can be refilled
       if constexpr (k >= PB)
         static_for<k + D - PB, (k + D < 16 ? k + D : 16)>([&](auto pc) {
@@ -778,6 +808,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
             yn[p] = get_y0<STREAM>(at_node(a.f0, p * a.plane + row0, lane_bytes));
           });
     }
+    if constexpr (WENO && k % PB == 0 && k > 0) static_for<k - PB, k>(weno_finish);
     const T* buf = slot(ic<k>{});
     f[k] = buf[cN];
     n += f[k];
@@ -786,7 +817,20 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
     // phi direction: sum_o uw5(o) f_{s+o}, upwind side by the sign of v_j
     T dph, dth;
     if constexpr (WENO) {
-      weno_advection<T, i, j, k>(buf + cN, Jnb, inv_rJdth, n_ref, dph, dth);
+      constexpr int h = (k / PB) & 1, p = k % PB;
+      const T rest = n_ref * T(rest_offset<T>(k));
+      face_p[p] = weno_face<T, j >= 2>([&](int o) { return buf[cN + o]; });
+      face_t[p] = weno_face<T, i >= 2>([&](int o) { return Jnb[o + 2] * (buf[cN + o * LXT] + rest); });
+      sFaceP[h][p][ly * (TX + 1) + lx + 1] = face_p[p];
+      sFaceT[h][p][(ly + 1) * TX + lx] = face_t[p];
+      if (wave == p) {  // the lower edge: the face below the tile's first row
+        const T* e = buf + (HY - 1) * LXT + lx + CX;
+        sFaceT[h][p][lx] =
+            weno_face<T, i >= 2>([&](int o) { return Jedge[o + 2] * (e[o * LXT] + rest); });
+      } else if (wave == PB + p && lx < TY) {  // the left edge, a lane per row
+        const T* e = buf + (lx + HY) * LXT + CX - 1;
+        sFaceP[h][p][lx * (TX + 1)] = weno_face<T, j >= 2>([&](int o) { return e[o]; });
+      }
     } else {
     dph = uw5_difference<T, j >= 2>([&](int o) { return buf[cN + o]; });
     // theta direction: sum_o uw5(o) J_{q+o} / (r J_q dtheta) f_{q+o}
@@ -797,10 +841,10 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
       constexpr int o = decltype(oc)::value;
       dth = fused(bth(o), buf[cN + (lo + o) * LXT], dth);
     });
-    }
     adv[k] = advection<T>(theta_first(i, j), fuse_constant(i, j), dth, dph, T(vel(i)),
-                          T(-vel(j)) * inv_Jdph, WENO ? T(0) : n_ref * T(rest_offset<T>(k)),
+                          T(-vel(j)) * inv_Jdph, n_ref * T(rest_offset<T>(k)),
                           i >= 2 ? rc.bsum_p : rc.bsum_m);
+    }
     if (ring) {
       const T fr = buf[cR];
       rn += fr;
@@ -809,7 +853,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
     }
     // keep the arithmetic of this population here: without the pin the compiler sinks it to
     // the end of the kernel and holds every stencil value of all 16 populations live
-    pin_reg(adv[k]);
+    if constexpr (!WENO) pin_reg(adv[k]);
     pin_reg(f[k]);
     pin_reg(n);
     pin_reg(nut);
@@ -818,6 +862,10 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
     pin_reg(rut);
     pin_reg(rup);
   });
+  if constexpr (WENO) {
+    __syncthreads();
+    static_for<16 - PBW, 16>(weno_finish);
+  }
 
   // ---- FP32: the order-parameter tiles hold the stage input's deviation (sPhi) and the base
   //      (sPhiB); their sum, the order parameter itself, replaces the base tile.  dsn is the
