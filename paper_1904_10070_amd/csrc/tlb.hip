@@ -482,9 +482,10 @@ __device__ __forceinline__ P* at_node(P* base, long long uniform_elems, unsigned
   return reinterpret_cast<P*>(reinterpret_cast<C*>(base + uniform_elems) + lane_bytes);
 }
 
-// Streaming (nontemporal) accesses for the stage outputs and the y^n loads, used on grids whose
-// state copies are far larger than the 256 MB last-level cache: there the output streams gain
-// nothing from being cached, while on grids that fit it the next stage reads them from there.
+// Streaming (nontemporal) accesses, used on grids whose state copies are larger than the 256 MB
+// last-level cache: for the stage outputs (STREAM 1) and also the y^n loads (STREAM 2).  There the
+// streams gain nothing from being cached and evict what would; on grids that fit it the next stage
+// reads them from there.  See streaming_level for where the lines lie.
 template <bool NT, typename T>
 __device__ __forceinline__ void put(T* p, T v) {
   if constexpr (NT)
@@ -639,7 +640,7 @@ struct Ring {
 // described by `a`, by a block of Tile<TY>::NT threads.  GENREF: the FP32 storage reference
 // density is read from the arguments; otherwise it is the constant 1 (every grid near unit
 // density), whose products the compiler folds away.
-template <typename T, bool VEC, int TY, bool WENO = false, bool STREAM = false,
+template <typename T, bool VEC, int TY, bool WENO = false, int STREAM = 0,
           bool GENREF = false, bool CH4 = false>
 __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, const int ty) {
 // (the body is device code: the host pass of the single-source compiler skips it; with both
@@ -740,7 +741,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
   const unsigned lane_bytes = (unsigned)(s < np ? s : 0) * (unsigned)sizeof(T);
   T phin = T(0);
   if constexpr (PF)
-    if (a.has_y0) phin = get_y0<STREAM>(at_node(a.phi0, row0, lane_bytes));
+    if (a.has_y0) phin = get_y0<(STREAM == 2)>(at_node(a.phi0, row0, lane_bytes));
   // moments of this node and of the ring node, both summed population by population in the
   // same order, so that a node's moments (and all that follows) do not depend on whether it
   // is inside a tile or in a neighbour's ring -- results are independent of the tile shape
@@ -805,7 +806,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
         if (a.has_y0)
           static_for<k, k + PB>([&](auto pc) {
             constexpr int p = decltype(pc)::value;
-            yn[p] = get_y0<STREAM>(at_node(a.f0, p * a.plane + row0, lane_bytes));
+            yn[p] = get_y0<(STREAM == 2)>(at_node(a.f0, p * a.plane + row0, lane_bytes));
           });
     }
     if constexpr (WENO && k % PB == 0 && k > 0) static_for<k - PB, k>(weno_finish);
@@ -928,9 +929,9 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
     const T own = stores_deviation<T>() ? dsn : phc;
     T yn0 = phin;
     if constexpr (!PF)
-      if (y0) yn0 = *at_node(a.phi0, row0, lane_bytes);
+      if (y0) yn0 = get_y0<(STREAM == 2)>(at_node(a.phi0, row0, lane_bytes));
     const T out = phi_update(own, yn0, Lphi, dt, a0, b1, y0);
-    put<STREAM>(at_node(a.phiout, row0, lane_bytes), out);
+    put<(STREAM > 0)>(at_node(a.phiout, row0, lane_bytes), out);
   }
 
   // ---- equilibrium, force and connection terms, Runge-Kutta combine
@@ -961,10 +962,12 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
     if (active) {
       T* dst = at_node(a.fout, k * a.plane + row0, lane_bytes);
       if constexpr (PF)
-        put<STREAM>(dst, y0 ? products(a0, yn[k], b1, ys) : ys);
+        put<(STREAM > 0)>(dst, y0 ? products(a0, yn[k], b1, ys) : ys);
       else
-        put<STREAM>(dst, y0 ? products(a0, *at_node(a.f0, k * a.plane + row0, lane_bytes), b1, ys)
-                            : ys);
+        put<(STREAM > 0)>(
+            dst, y0 ? products(a0, get_y0<(STREAM == 2)>(at_node(a.f0, k * a.plane + row0, lane_bytes)),
+                               b1, ys)
+                    : ys);
     }
   });
 #endif
@@ -983,7 +986,7 @@ struct StageWaves {
   static constexpr int value = sizeof(T) == 4 ? TLB_WPE32 : TLB_WPE64;
 };
 
-template <typename T, bool VEC, int TY, bool WENO = false, bool STREAM = false,
+template <typename T, bool VEC, int TY, bool WENO = false, int STREAM = 0,
           bool GENREF = false, bool CH4 = false>
 __global__ __launch_bounds__(Tile<TY>::NT) __attribute__((amdgpu_waves_per_eu(
     StageWaves<T>::value))) void tlb_stage_kernel(StageArgs<T> a) {
@@ -1326,7 +1329,7 @@ __device__ __forceinline__ P* global_ptr(P* p) {
   return (P*)((__attribute__((address_space(1))) P*)reinterpret_cast<uintptr_t>(p));
 }
 
-template <typename T, bool VEC, int TY, bool GENREF = false, bool STREAM = false>
+template <typename T, bool VEC, int TY, bool GENREF = false, int STREAM = 0>
 __global__ __launch_bounds__(Tile<TY>::NT) __attribute__((amdgpu_waves_per_eu(
     StageWaves<T>::value))) void tlb_stage_batch_kernel(
     const StageArgs<T>* __restrict__ table, const int* __restrict__ tile_begin, int n, int stage) {
@@ -1978,7 +1981,7 @@ struct tlb_batch {
   int* tile_begin;  // [n + 1] (device)
   int total_tiles;
   hipGraphExec_t graphs[GRAPH_CHUNK_B + 1];  // as tlb_grid::graphs, for the whole batch
-  bool streaming;      // the ensemble's state copies exceed STREAMING_BYTES
+  int streaming;       // streaming_level of the ensemble's state copies
   unsigned* versions;  // [n]: the grids' versions when the table was built
 };
 
@@ -2021,22 +2024,23 @@ bool vec_ok(int n_phi) {
   return n_phi % (16 / (int)sizeof(T)) == 0;
 }
 
-template <typename T, bool VEC, bool GENREF>
-const void* stage_fn_ty(int ty, bool streaming) {
-  if (streaming) {  // the 16-byte-copy form only (every large grid here has n_phi % 4 == 0)
-    if constexpr (VEC) {
-      switch (ty) {
-        case 4: return reinterpret_cast<const void*>(&tlb_stage_kernel<T, true, 4, false, true, GENREF>);
-        case 16: return reinterpret_cast<const void*>(&tlb_stage_kernel<T, true, 16, false, true, GENREF>);
-        default: return reinterpret_cast<const void*>(&tlb_stage_kernel<T, true, 8, false, true, GENREF>);
-      }
-    }
-  }
+template <typename T, bool VEC, bool GENREF, int STREAM>
+const void* stage_fn_ty(int ty) {
   switch (ty) {
-    case 4: return reinterpret_cast<const void*>(&tlb_stage_kernel<T, VEC, 4, false, false, GENREF>);
-    case 16: return reinterpret_cast<const void*>(&tlb_stage_kernel<T, VEC, 16, false, false, GENREF>);
-    default: return reinterpret_cast<const void*>(&tlb_stage_kernel<T, VEC, 8, false, false, GENREF>);
+    case 4: return reinterpret_cast<const void*>(&tlb_stage_kernel<T, VEC, 4, false, STREAM, GENREF>);
+    case 16: return reinterpret_cast<const void*>(&tlb_stage_kernel<T, VEC, 16, false, STREAM, GENREF>);
+    default: return reinterpret_cast<const void*>(&tlb_stage_kernel<T, VEC, 8, false, STREAM, GENREF>);
   }
+}
+// streaming: the 16-byte-copy form only (large grids have n_phi % 4 == 0); FP32 has levels 0 and 2
+template <typename T, bool VEC, bool GENREF>
+const void* stage_fn_stream(int ty, int level) {
+  if constexpr (VEC) {
+    if (level == 2) return stage_fn_ty<T, true, GENREF, 2>(ty);
+    if constexpr (sizeof(T) == 8)
+      if (level == 1) return stage_fn_ty<T, true, GENREF, 1>(ty);
+  }
+  return stage_fn_ty<T, VEC, GENREF, 0>(ty);
 }
 
 // FP32 grids whose reference density is not 1 need the kernels that read it
@@ -2045,12 +2049,19 @@ bool general_reference(const tlb_grid* g) {
   return stores_deviation<T>() && g->n_ref != 1.0;
 }
 
-// Grids whose three state copies (51 values per node) exceed this use streaming accesses
-constexpr double STREAMING_BYTES = 1024.0 * 1024.0 * 1024.0;
-
-bool streaming(const tlb_grid* g) {
-  return 51.0 * g->p.n_theta * (double)g->p.n_phi * (double)g->elem > STREAMING_BYTES;
+// The streaming level of grids (or ensembles) whose three state copies, 51 values per node, take
+// `bytes`.  Times per step in us at levels 0 / 1 / 2.  FP64: 267 MB 137 / 149 / 170, 334 MB 215 / 190
+// / 219, 522 MB 348 / 310 / 318, 668 MB 450 / 431 / 426, 1069 MB 704 / 688 / 673.  FP32: 334 MB
+// 200 / 206 / 209, 427 MB 270 / 268 / 270, 534 MB 356 / 333 / 332, 835 MB 539 / 528 / 513 (1 GiB was
+// the line before).
+int streaming_level(double bytes, size_t elem) {
+  if (elem == 4) return bytes > 430e6 ? 2 : 0;
+  return bytes > 600e6 ? 2 : bytes > 300e6 ? 1 : 0;
 }
+double state_bytes(const tlb_grid* g) {
+  return 51.0 * g->p.n_theta * (double)g->p.n_phi * (double)g->elem;
+}
+int streaming(const tlb_grid* g) { return streaming_level(state_bytes(g), g->elem); }
 
 // The small-grid kernel runs grids of at most this many 64-node row segments (not WENO-5, whose
 // arithmetic outweighs the latencies).  Times per step in us, tiles / small-grid kernel: FP32, 960
@@ -2093,41 +2104,41 @@ const void* stage_fn(const tlb_grid* g) {
                : reinterpret_cast<const void*>(&tlb_stage_kernel<T, false, DEFAULT_TY, true>);
   }
   if (gen)
-    return vec ? stage_fn_ty<T, true, true>(g->ty, streaming(g))
-               : stage_fn_ty<T, false, true>(g->ty, streaming(g));
-  return vec ? stage_fn_ty<T, true, false>(g->ty, streaming(g))
-             : stage_fn_ty<T, false, false>(g->ty, streaming(g));
+    return vec ? stage_fn_stream<T, true, true>(g->ty, streaming(g))
+               : stage_fn_stream<T, false, true>(g->ty, streaming(g));
+  return vec ? stage_fn_stream<T, true, false>(g->ty, streaming(g))
+             : stage_fn_stream<T, false, false>(g->ty, streaming(g));
 }
 
-template <typename T, bool VEC, bool GENREF>
-const void* batch_fn_ty(int ty, bool streaming) {
-  if (streaming) {  // as for single grids, the 16-byte-copy form only
-    if constexpr (VEC) {
-      switch (ty) {
-        case 4: return reinterpret_cast<const void*>(&tlb_stage_batch_kernel<T, true, 4, GENREF, true>);
-        case 16: return reinterpret_cast<const void*>(&tlb_stage_batch_kernel<T, true, 16, GENREF, true>);
-        default: return reinterpret_cast<const void*>(&tlb_stage_batch_kernel<T, true, 8, GENREF, true>);
-      }
-    }
-  }
+template <typename T, bool VEC, bool GENREF, int STREAM>
+const void* batch_fn_ty(int ty) {
   switch (ty) {
-    case 4: return reinterpret_cast<const void*>(&tlb_stage_batch_kernel<T, VEC, 4, GENREF>);
-    case 16: return reinterpret_cast<const void*>(&tlb_stage_batch_kernel<T, VEC, 16, GENREF>);
-    default: return reinterpret_cast<const void*>(&tlb_stage_batch_kernel<T, VEC, 8, GENREF>);
+    case 4: return reinterpret_cast<const void*>(&tlb_stage_batch_kernel<T, VEC, 4, GENREF, STREAM>);
+    case 16: return reinterpret_cast<const void*>(&tlb_stage_batch_kernel<T, VEC, 16, GENREF, STREAM>);
+    default: return reinterpret_cast<const void*>(&tlb_stage_batch_kernel<T, VEC, 8, GENREF, STREAM>);
   }
+}
+template <typename T, bool VEC, bool GENREF>
+const void* batch_fn_stream(int ty, int level) {  // as for single grids
+  if constexpr (VEC) {
+    if (level == 2) return batch_fn_ty<T, true, GENREF, 2>(ty);
+    if constexpr (sizeof(T) == 8)
+      if (level == 1) return batch_fn_ty<T, true, GENREF, 1>(ty);
+  }
+  return batch_fn_ty<T, VEC, GENREF, 0>(ty);
 }
 
 // the batch kernel for the batch's current grids (the general-reference form if any needs it;
-// streaming accesses when the ensemble's state copies together exceed STREAMING_BYTES)
+// streaming accesses by the size of the ensemble's state copies together)
 template <typename T>
 const void* batch_fn(const tlb_batch* b) {
   bool gen = false;
   for (int i = 0; i < b->n; ++i) gen = gen || general_reference<T>(b->grids[i]);
   if (gen)
-    return b->vec ? batch_fn_ty<T, true, true>(b->ty, b->streaming)
-                  : batch_fn_ty<T, false, true>(b->ty, b->streaming);
-  return b->vec ? batch_fn_ty<T, true, false>(b->ty, b->streaming)
-                : batch_fn_ty<T, false, false>(b->ty, b->streaming);
+    return b->vec ? batch_fn_stream<T, true, true>(b->ty, b->streaming)
+                  : batch_fn_stream<T, false, true>(b->ty, b->streaming);
+  return b->vec ? batch_fn_stream<T, true, false>(b->ty, b->streaming)
+                : batch_fn_stream<T, false, false>(b->ty, b->streaming);
 }
 
 int stage_blocks(const tlb_grid* g) {
@@ -3204,14 +3215,14 @@ int32_t tlb_create_batch(tlb_grid* const* grids, int32_t n, void* hip_stream, tl
   b->ty = DEFAULT_TY;
   b->stream = static_cast<hipStream_t>(hip_stream);
   b->vec = true;
-  double state_bytes = 0.0;
+  double bytes = 0.0;
   for (int i = 0; i < n; ++i) {
     b->grids[i] = grids[i];
     b->vec = b->vec && (b->precision == 64 ? vec_ok<double>(grids[i]->p.n_phi)
                                            : vec_ok<float>(grids[i]->p.n_phi));
-    state_bytes += 51.0 * grids[i]->p.n_theta * (double)grids[i]->p.n_phi * (double)grids[i]->elem;
+    bytes += state_bytes(grids[i]);
   }
-  b->streaming = state_bytes > STREAMING_BYTES;
+  b->streaming = streaming_level(bytes, grids[0]->elem);
   const size_t args_bytes = b->precision == 64 ? sizeof(StageArgs<double>) : sizeof(StageArgs<float>);
   hipError_t e = hipMalloc(&b->table, args_bytes * 3 * n);
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&b->tile_begin), sizeof(int) * (n + 1));
