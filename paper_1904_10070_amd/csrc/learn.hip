@@ -14,10 +14,11 @@
 //                             during a tile's products.  The input gradient is the same
 //                             kernel with the weights transposed and the taps mirrored.
 //   weight gradient           one workgroup = strips of 64 nodes of a row; the error signal
-//                             and the nine shifted input tiles are transposed into LDS so that
-//                             the contraction over nodes reads 8 consecutive nodes per lane;
-//                             the next strip's loads are in flight during a strip's products;
-//                             per-workgroup partial sums are added in a fixed order (FP64).
+//                             and the input rows are staged in LDS as they are in memory, and
+//                             transposing LDS reads give each lane the 8 consecutive nodes of
+//                             its operand; the next strip's loads are in flight during a
+//                             strip's products; per-workgroup partial sums are added in a
+//                             fixed order (FP64).
 // Grids are sized at network creation from the occupancy of each kernel: one wave of resident
 // workgroups where the per-workgroup set-up is large (weight gradient, 32-channel inputs).
 // Activations are bfloat16, channel-last [sample][theta][phi][channel].
@@ -329,10 +330,10 @@ void conv_kernel(ConvArgs a) {
 // ------------------------------------------------------------------------------------------
 // weight gradient: dW[o][t][i] = sum over nodes of e[node][o] a[node + offset(t)][i]
 
-constexpr int WG_PITCH = 72;  // LDS row pitch (bf16): 64 nodes + 8 keeps rows 16-byte aligned
-// bf16 index of node j of row r
-__device__ __forceinline__ int wg_at(int r, int j) { return r * WG_PITCH + j; }
 constexpr int WG_THREADS = 256;
+// workgroups per compute unit: as many as one wave of resident workgroups of each kernel's first
+// form; the number fixes the order of the gradient's sums, so it stays
+constexpr int wgrad_per_cu(int cis) { return cis == 8 ? 5 : 3; }
 
 struct WgradArgs {
   const u16* e;        // error signal bf16 [n][H][W][COS]
@@ -363,162 +364,126 @@ struct StripPos {
   }
 };
 
-// The input tiles in LDS form a window of three rows: tap (dy, dx) of the strip in row y
-// (input row y + dy - 1, nodes shifted by dx - 1) sits in tile 3 slot + dx with slot =
-// (y + dy + 2) mod 3.  The next row's strip of the same column shares two of the rows, so
-// it stages only the new one (its three taps dy = 2); a strip that starts a column stages
-// all nine taps.
-__device__ __forceinline__ int wg_tile(int y, int t) { return ((y + t / 3 + 2) % 3) * 3 + t % 3; }
+// Four nodes of one channel per lane from a tile of C channels per node (channel-last, in LDS):
+// the 16 lanes of group g get channels ch0 .. ch0 + 15 (lane px: ch0 + px) of nodes j0 .. j0 + 3.
+// The transposing read gives lane t of a group the values t % 4 of the group's lanes t / 4, 4 +
+// t / 4, 8 + t / 4 and 12 + t / 4, so lane px reads channels ch0 + 4 (px % 4) .. + 3 of node
+// j0 + px / 4.  Two of them are the eight consecutive nodes of a lane's operand.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+template <int C>
+__device__ __forceinline__ bf16x8 node_operand(const u16* tile, int j0, int ch0, int px) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  const u16* p = tile + (j0 + (px >> 2)) * C + ch0 + 4 * (px & 3);
+  union {
+    s16x4 h[2];
+    bf16x8 v;
+  } u;
+  u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+  u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * C));
+  return u.v;
+#else
+  return bf16x8{};
+#endif
+}
 
-// The global loads of one strip, all issued before any is used: the error tile (thread u <
-// (COS/8) 64 takes node u % 64, channels 8 (u / 64) .. + 7) and the input taps to stage, by
-// pairs of neighbouring nodes (unit u: nodes 2 (u % 32) and +1, channels 8 c8 .. + 7 with
-// c8 = (u / 32) % (CIS / 8), tap T0 + (u / 32) / (CIS / 8), so that each LDS store of the
-// transposed tile writes two consecutive nodes); the error is zero beyond the row's end.
-// With CIS / 8 even, the 64 units of a wavefront share their tap: the taps are then found
-// once per thread, from the wavefront index, and are scalars.  The partial last round of
-// units goes to the highest threads: the products give the lowest wavefronts the extra
-// (tap, input block) pair, so the SIMDs even out.
-template <int CIS, int NTAP, int T0>
-struct WgradUnits {
-  static constexpr int NA = NTAP * (CIS / 8) * 32;
-  static constexpr int KA = (NA + WG_THREADS - 1) / WG_THREADS;
-  static constexpr int REM = NA - (KA - 1) * WG_THREADS;
-  static constexpr bool UNIFORM = (CIS / 8) % 2 == 0;
-  int tap[KA];  // UNIFORM: tap of unit k, 9 where the thread has no unit k
-
-  // first unit of round k (units base .. base + WG_THREADS - 1 by thread)
-  __device__ __forceinline__ static int base_of(int k) {
-    return k < KA - 1 ? k * WG_THREADS : k * WG_THREADS - (WG_THREADS - REM);
-  }
-  __device__ __forceinline__ static int unit_of(int k) {
-    return (k < KA - 1 || (int)threadIdx.x >= WG_THREADS - REM) ? base_of(k) + (int)threadIdx.x
-                                                                : -1;
-  }
-  __device__ __forceinline__ void init(int wave) {
-    if constexpr (UNIFORM) {
-#pragma unroll
-      for (int k = 0; k < KA; ++k) {
-        // (u / 32) / (CIS / 8) with u / 32 = base / 32 + 2 wave + lane / 32, base / 32 even:
-        // the lane's bit drops
-        const bool has = k < KA - 1 || 64 * wave >= WG_THREADS - REM;
-        tap[k] = has ? T0 + ((base_of(k) >> 6) + wave) / (CIS / 16) : 9;
-      }
-    }
-  }
-  __device__ __forceinline__ int tap_of(int k) const {
-    if constexpr (UNIFORM) return tap[k];
-    const int u = unit_of(k);
-    return u >= 0 ? T0 + (u >> 5) / (CIS / 8) : 9;
-  }
-};
-
+// The tiles stay as they are in memory, channel-last: the contraction's operands, eight nodes per
+// lane, come from transposing reads, and a tap shifted by a node is the same tile read a node
+// further, so a strip stages its error (64 nodes) and one new input row (66 nodes with the
+// neighbours) with 16-byte accesses.  Transposed on the way into LDS instead, with one copy per
+// shift, the staging was three quarters of a strip's LDS accesses.  The error is kept twice and
+// the input rows in a ring of four, so that the next strip is stored while others still read: one
+// barrier per strip instead of two.
+//
+// 16 x 128 x 320 nodes: 32 -> 32 channels 25.9 us (31.8 with the transposed tiles), 32 -> 4 18.6
+// (25.4), 6 -> 32 19.8 (20.0).  The 32 -> 32 layer moves 112 MB (activations 42, errors 42, the
+// partial sums of 768 workgroups 28), 17 us at the rate of a large copy; the rest is the
+// workgroups' start and end, 13 strips apart.  Loads two strips ahead gave nothing (27.0, 19.2,
+// 20.9: more registers, fewer wavefronts).
 template <int CIS, int COS>
 struct WgradStrip {
-  static constexpr int NE = (COS / 8) * 64;
-  using Full = WgradUnits<CIS, 9, 0>;  // a strip that starts a column: all nine taps
-  using Row = WgradUnits<CIS, 3, 6>;   // the next row's strip: the new row's three taps
-  static constexpr int KA = Full::KA;
-  // every round starts at a multiple of 32 (CIS / 8) units, so a thread's node pair and
-  // channel group are the same in both modes; only the taps differ
-  static_assert(Full::REM % (32 * (CIS / 8)) == 0 && Row::REM % (32 * (CIS / 8)) == 0,
-                "round bases");
+  static constexpr int CA = CIS / 8, CE = COS / 8;  // 16-byte chunks per node
+  static constexpr int NA = 66 * CA, NE = 64 * CE;  // chunks of an input row and of the error
+  static constexpr int KA = (NA + WG_THREADS - 1) / WG_THREADS;
+  // an input row: its 66 nodes and what the operands of channels past CIS (not used) read beyond
+  static constexpr int ROW = 66 * CIS + 16;
+  static constexpr int ERR = 64 * COS + 16;
   uint4 e;
-  uint4 av[KA][2];  // bf16 inputs of the two nodes
-  Full full;
-  Row row;
+  uint4 av[KA];
 
-  __device__ __forceinline__ void init(int wave) {
-    full.init(wave);
-    row.init(wave);
+  // chunk k of this thread in an input row: its LDS place, and its place in memory.  One wrap is
+  // exact for the nodes that the row's own use; those further on, whose error is zero, read the
+  // row's last node.  (Threads without a chunk read the last one again.)
+  __device__ __forceinline__ static int chunk(int k) {
+    return min((int)threadIdx.x + k * WG_THREADS, NA - 1);
   }
-  // tap of this thread's unit in round k (9: none) when staging all taps or the new row's
-  __device__ __forceinline__ int tap_of(int k, bool all) const {
-    const int tr = k < Row::KA ? row.tap_of(k) : 9;
-    return all ? full.tap_of(k) : tr;
-  }
-
-  __device__ __forceinline__ void load(const WgradArgs& a, const StripPos& p, bool all) {
-    const int y = p.y, n = p.n;
-    const int x0 = p.xb * 64;
-    const int jp = threadIdx.x & 31, c8 = (threadIdx.x >> 5) % (CIS / 8);
-    e = make_uint4(0, 0, 0, 0);
+  __device__ __forceinline__ static uint4 load_chunk(const WgradArgs& a, int n, int y, int x0,
+                                                     int c) {
     // bf16 tensors: n H W < 2^28 nodes, checked when the network is created; each load takes
     // its row's start (uniform) and a 32-bit byte offset within the row
-    if (threadIdx.x < NE) {
-      const int j = threadIdx.x & 63, c8e = threadIdx.x >> 6;
-      const char* erow =
-          reinterpret_cast<const char*>(a.e) + (size_t)((n * a.H + y) * a.W) * COS * 2;
-      if (x0 + j < a.W)
-        e = *reinterpret_cast<const uint4*>(erow + (unsigned)(((x0 + j) * COS + 8 * c8e) * 2));
-    }
+    const int xx = min(wrap1(x0 + c / CA - 1, a.W), a.W - 1);
+    const char* row = reinterpret_cast<const char*>(a.a) + (size_t)((n * a.H + y) * a.W) * CIS * 2;
+    return *reinterpret_cast<const uint4*>(row + (unsigned)((xx * CIS + 8 * (c % CA)) * 2));
+  }
+  // the error and the input row y + 1
+  __device__ __forceinline__ void load(const WgradArgs& a, const StripPos& p) {
+    const int x0 = p.xb * 64, u = min((int)threadIdx.x, NE - 1);
+    const int x = min(x0 + u / CE, a.W - 1);
+    const char* row =
+        reinterpret_cast<const char*>(a.e) + (size_t)((p.n * a.H + p.y) * a.W) * COS * 2;
+    e = *reinterpret_cast<const uint4*>(row + (unsigned)((x * COS + 8 * (u % CE)) * 2));
 #pragma unroll
-    for (int k = 0; k < KA; ++k) {
-      const int t = tap_of(k, all);
-      if (t < 9) {
-        const int yy = wrap1(y + t / 3 - 1, a.H);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          // one wrap is exact for the row's nodes (x0 + 2 jp + h < W); those past its end,
-          // whose error is zero, read the row's last node
-          const int xx = min(wrap1(x0 + 2 * jp + h + t % 3 - 1, a.W), a.W - 1);
-          const char* arow =
-              reinterpret_cast<const char*>(a.a) + (size_t)((n * a.H + yy) * a.W) * CIS * 2;
-          av[k][h] = *reinterpret_cast<const uint4*>(arow + (unsigned)((xx * CIS + 8 * c8) * 2));
-        }
-      }
-    }
+    for (int k = 0; k < KA; ++k) av[k] = load_chunk(a, p.n, wrap1(p.y + 1, a.H), x0, chunk(k));
   }
 
-  // transposed into LDS: sE[o][j] = e[n][y][x0 + j][o]; tile wg_tile(y, t) of sA [i][j] =
-  // a[n][y + dy - 1][x0 + j + dx - 1][i]; bsum[i] accumulates this thread's error values
-  // (channel 8 (tid / 64) + i)
-  __device__ __forceinline__ void store(const WgradArgs& a, const StripPos& p, bool all, u16* sE,
-                                        u16* sA, float (&bsum)[8]) const {
-    if (threadIdx.x < NE) {
-      const int j = threadIdx.x & 63, c8e = threadIdx.x >> 6;
-      const unsigned w4[4] = {e.x, e.y, e.z, e.w};
+  // into LDS, with the error zero beyond the row's end; bsum[i] accumulates this thread's error
+  // values (channel 8 (tid % CE) + i)
+  __device__ __forceinline__ void store(const WgradArgs& a, const StripPos& p, u16* sE, u16* sA,
+                                        float (&bsum)[8]) const {
+    const int u = threadIdx.x;
+    if (u < NE) {
+      const unsigned live = p.xb * 64 + u / CE < a.W ? ~0u : 0u;
+      const unsigned w4[4] = {e.x & live, e.y & live, e.z & live, e.w & live};
+      *reinterpret_cast<uint4*>(sE + 8 * u) = make_uint4(w4[0], w4[1], w4[2], w4[3]);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const u16 v = (u16)((w4[i >> 1] >> (16 * (i & 1))) & 0xFFFF);
-        sE[wg_at(8 * c8e + i, j)] = v;
-        bsum[i] += from_bf16(v);
-      }
+      for (int i = 0; i < 8; ++i)
+        bsum[i] += from_bf16((u16)((w4[i >> 1] >> (16 * (i & 1))) & 0xFFFF));
     }
-    const int jp = threadIdx.x & 31, c8 = (threadIdx.x >> 5) % (CIS / 8);
 #pragma unroll
-    for (int k = 0; k < KA; ++k) {
-      const int t = tap_of(k, all);
-      if (t < 9) {
-        // the two nodes' channels 8 c8 .. + 7, two bf16 per word
-        const unsigned w[2][4] = {{av[k][0].x, av[k][0].y, av[k][0].z, av[k][0].w},
-                                  {av[k][1].x, av[k][1].y, av[k][1].z, av[k][1].w}};
-        // channel 2 i: the low halves of the two nodes' word i; channel 2 i + 1: the high
-        // halves (byte selectors 0-3 take the second operand's bytes, 4-7 the first's)
-        const int tile = wg_tile(p.y, t);
+    for (int k = 0; k < KA; ++k)
+      if (u + k * WG_THREADS < NA)
+        *reinterpret_cast<uint4*>(sA + ((p.y + 2) & 3) * ROW + 8 * (u + k * WG_THREADS)) = av[k];
+  }
+  // the rows y - 1 and y of a strip that starts a column (or is a workgroup's first)
+  __device__ __forceinline__ static void column_start(const WgradArgs& a, const StripPos& p,
+                                                      u16* sA) {
+    uint4 v[2][KA];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          // rows 2 i and 2 i + 1 of the group share their chunk order
-          unsigned* r =
-              reinterpret_cast<unsigned*>(sA + wg_at(tile * CIS + 8 * c8 + 2 * i, 2 * jp));
-          r[0] = __builtin_amdgcn_perm(w[1][i], w[0][i], 0x05040100u);
-          r[WG_PITCH / 2] = __builtin_amdgcn_perm(w[1][i], w[0][i], 0x07060302u);
-        }
-      }
-    }
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+      for (int k = 0; k < KA; ++k)
+        v[d][k] = load_chunk(a, p.n, wrap1(p.y + d - 1, a.H), p.xb * 64, chunk(k));
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+      for (int k = 0; k < KA; ++k)
+        *reinterpret_cast<uint4*>(sA + ((p.y + d) & 3) * ROW + 8 * chunk(k)) = v[d][k];
   }
 };
 
 template <int CIS, int COS>
-__global__ __launch_bounds__(WG_THREADS) void wgrad_kernel(WgradArgs a) {
+__global__ __launch_bounds__(WG_THREADS) __attribute__((amdgpu_waves_per_eu(wgrad_per_cu(CIS))))
+void wgrad_kernel(WgradArgs a) {
   constexpr int CIB = (CIS + 15) / 16, COB = (COS + 15) / 16;
   // 16 x 16 output fragments (tap t, output block bc, input block bi); a wavefront takes
   // whole (t, bi) pairs, so that each node operand it reads from LDS serves every bc
   constexpr int NP = 9 * CIB;            // (tap, input block) pairs
   constexpr int PPW = (NP + 3) / 4;      // pairs per wavefront
   using Strip = WgradStrip<CIS, COS>;
-  __shared__ __attribute__((aligned(16))) u16 sE[COS * WG_PITCH];
-  __shared__ __attribute__((aligned(16))) u16 sA[9 * CIS * WG_PITCH];
+  __shared__ __attribute__((aligned(16))) u16 sE[2 * Strip::ERR];
+  // four rows; in the end the error's sums per node and channel (floats)
+  constexpr int SA = 4 * Strip::ROW > 128 * COS ? 4 * Strip::ROW : 128 * COS;
+  __shared__ __attribute__((aligned(16))) u16 sA[SA];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3;
   const int px = lane & 15, g = lane >> 4;
@@ -530,26 +495,21 @@ __global__ __launch_bounds__(WG_THREADS) void wgrad_kernel(WgradArgs a) {
   float bsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const int s0 = (int)((long long)blockIdx.x * a.strips / gridDim.x);
   const int s1 = (int)((long long)(blockIdx.x + 1) * a.strips / gridDim.x);
-  auto products = [&](int y) {
+  auto products = [&](const u16* E, int y) {
     bf16x8 A[COB][2];  // the error operand of every output block, both halves of the strip
 #pragma unroll
     for (int bc = 0; bc < COB; ++bc)
 #pragma unroll
-      for (int kc = 0; kc < 2; ++kc)
-        A[bc][kc] = 16 * bc + px < COS ? *reinterpret_cast<const bf16x8*>(
-                                             &sE[wg_at(16 * bc + px, 32 * kc + 8 * g)])
-                                       : zero_frag();
+      for (int kc = 0; kc < 2; ++kc) A[bc][kc] = node_operand<COS>(E, 32 * kc + 8 * g, 16 * bc, px);
 #pragma unroll
     for (int k = 0; k < PPW; ++k) {
       const int pr = wave + 4 * k;
       if (pr < NP) {
         const int t = pr / CIB, bi = pr % CIB;
-        const int ci = 16 * bi + px;
+        const u16* row = sA + ((y + t / 3) & 3) * Strip::ROW;
 #pragma unroll
         for (int kc = 0; kc < 2; ++kc) {
-          const bf16x8 B = ci < CIS ? *reinterpret_cast<const bf16x8*>(
-                                          &sA[wg_at(wg_tile(y, t) * CIS + ci, 32 * kc + 8 * g)])
-                                    : zero_frag();
+          const bf16x8 B = node_operand<CIS>(row, 32 * kc + 8 * g + t % 3, 16 * bi, px);
 #pragma unroll
           for (int bc = 0; bc < COB; ++bc)
             acc[k][bc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[bc][kc], B, acc[k][bc], 0, 0, 0);
@@ -558,23 +518,22 @@ __global__ __launch_bounds__(WG_THREADS) void wgrad_kernel(WgradArgs a) {
     }
   };
   Strip st;
-  st.init(wave);
-  StripPos pos, nxt;
-  pos.set(s0, a.xs, a.H);
-  bool all = true;  // the strip stages all nine taps (the workgroup's first, or a new column)
-  if (s0 < s1) st.load(a, pos, all);
+  StripPos pos, nxt;  // of strips s and s + 1 (the last one again at the end)
+  pos.set(s0, a.xs, a.H);  // a workgroup has at least one strip
+  st.load(a, pos);
   for (int s = s0; s < s1; ++s) {
-    st.store(a, pos, all, sE, sA, bsum);
-    // the next strip's loads are in flight during this strip's products
+    u16* E = sE + (s & 1) * Strip::ERR;
+    if (s == s0 || pos.y == 0) {
+      if (s > s0) __syncthreads();  // the rows of the column before are still read
+      Strip::column_start(a, pos, sA);
+    }
+    st.store(a, pos, E, sA, bsum);
     nxt = pos;
-    nxt.next(a.xs, a.H);
-    const bool nall = nxt.y == 0;
-    if (s + 1 < s1) st.load(a, nxt, nall);
+    if (s + 1 < s1) nxt.next(a.xs, a.H);
+    st.load(a, nxt);
     __syncthreads();
-    products(pos.y);
-    __syncthreads();
+    products(E, pos.y);
     pos = nxt;
-    all = nall;
   }
   float* out = a.partial + (size_t)blockIdx.x * (COS * 9 * CIS + COS);
 #pragma unroll
@@ -592,15 +551,22 @@ __global__ __launch_bounds__(WG_THREADS) void wgrad_kernel(WgradArgs a) {
         }
     }
   }
-  // bias gradient: the error values of channel 8 w + i sit in wave w's lanes (one node each)
+  // bias gradient: a thread's sums belong to node tid / CE and channels 8 (tid % CE) .. + 7; wavefront
+  // w adds channels 8 w .. + 7 over the 64 nodes, a lane each
+  __syncthreads();
+  float* sB = reinterpret_cast<float*>(sA);  // [64][COS]
+  if (threadIdx.x < Strip::NE)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sB[8 * threadIdx.x + i] = bsum[i];
+  __syncthreads();
   if (threadIdx.x < Strip::NE) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 8; ++i) {
+      float v = sB[lane * COS + 8 * wave + i];
 #pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) bsum[i] += __shfl_xor(bsum[i], d, 64);
-    if (lane == 0)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) out[COS * 9 * CIS + 8 * wave + i] = bsum[i];
+      for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+      if (lane == 0) out[COS * 9 * CIS + 8 * wave + i] = v;
+    }
   }
 }
 
@@ -1819,16 +1785,10 @@ int32_t tlb_cnn_create(const tlb_cnn_desc* desc, void* hip_stream, tlb_cnn** out
       net->conv_grid[v] = (int)std::min<long long>(CONV_MAX_BLOCKS,
                                                    (long long)std::max(resident, 1) * cus);
   }
-  // Weight-gradient grids: one wave of resident workgroups (LDS or registers limit them to
-  // 3 to 5 per compute unit), each taking consecutive strips, the next strip's loads in
-  // flight during a strip's products.
-  for (int l = 0; l < NL && e == hipSuccess; ++l) {
-    int resident = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, wgrad_fn(l), WG_THREADS, 0);
-    if (e == hipSuccess)
-      net->wgrad_grid[l] =
-          (int)std::min<long long>(WG_MAX_BLOCKS, (long long)std::max(resident, 1) * cus);
-  }
+  // Weight-gradient grids, each workgroup taking consecutive strips: three per compute unit, five
+  // for the first layer, whose partial gradients are a quarter as large.  (More would be resident,
+  // but each writes its partial gradient and grad_reduce_kernel reads it: 28 MB at three per unit.)
+  for (int l = 0; l < NL; ++l) net->wgrad_grid[l] = std::min(WG_MAX_BLOCKS, wgrad_per_cu(L_CIS[l]) * cus);
   if (e != hipSuccess) {
     free_net(net);
     return tlbi_fail(TLB_EHIP, std::string("occupancy query: ") + hipGetErrorString(e));
