@@ -395,11 +395,11 @@ __device__ __forceinline__ bf16x8 node_operand(const u16* tile, int j0, int ch0,
 // the input rows in a ring of four, so that the next strip is stored while others still read: one
 // barrier per strip instead of two.
 //
-// 16 x 128 x 320 nodes: 32 -> 32 channels 25.9 us (31.8 with the transposed tiles), 32 -> 4 18.6
-// (25.4), 6 -> 32 19.8 (20.0).  The 32 -> 32 layer moves 112 MB (activations 42, errors 42, the
+// 16 x 128 x 320 nodes: 32 -> 32 channels 25.3 us (32.5 with the transposed tiles), 32 -> 4 19.2
+// (26.5), 6 -> 32 17.1 (20.3).  The 32 -> 32 layer moves 112 MB (activations 42, errors 42, the
 // partial sums of 768 workgroups 28), 17 us at the rate of a large copy; the rest is the
-// workgroups' start and end, 13 strips apart.  Loads two strips ahead gave nothing (27.0, 19.2,
-// 20.9: more registers, fewer wavefronts).
+// workgroups' start and end, 13 strips apart.  Loads two strips ahead gave nothing: more
+// registers, fewer wavefronts.
 template <int CIS, int COS>
 struct WgradStrip {
   static constexpr int CA = CIS / 8, CE = COS / 8;  // 16-byte chunks per node
@@ -482,7 +482,8 @@ void wgrad_kernel(WgradArgs a) {
   using Strip = WgradStrip<CIS, COS>;
   __shared__ __attribute__((aligned(16))) u16 sE[2 * Strip::ERR];
   // four rows; in the end the error's sums per node and channel (floats)
-  constexpr int SA = 4 * Strip::ROW > 128 * COS ? 4 * Strip::ROW : 128 * COS;
+  constexpr int SB = COS + 1;  // floats per node: an odd pitch spreads a channel over the banks
+  constexpr int SA = 4 * Strip::ROW > 128 * SB ? 4 * Strip::ROW : 128 * SB;
   __shared__ __attribute__((aligned(16))) u16 sA[SA];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3;
@@ -554,15 +555,16 @@ void wgrad_kernel(WgradArgs a) {
   // bias gradient: a thread's sums belong to node tid / CE and channels 8 (tid % CE) .. + 7; wavefront
   // w adds channels 8 w .. + 7 over the 64 nodes, a lane each
   __syncthreads();
-  float* sB = reinterpret_cast<float*>(sA);  // [64][COS]
+  float* sB = reinterpret_cast<float*>(sA);  // [64][SB]
   if (threadIdx.x < Strip::NE)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) sB[8 * threadIdx.x + i] = bsum[i];
+    for (int i = 0; i < 8; ++i)
+      sB[(threadIdx.x / Strip::CE) * SB + 8 * (threadIdx.x % Strip::CE) + i] = bsum[i];
   __syncthreads();
   if (threadIdx.x < Strip::NE) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      float v = sB[lane * COS + 8 * wave + i];
+      float v = sB[lane * SB + 8 * wave + i];
 #pragma unroll
       for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
       if (lane == 0) out[COS * 9 * CIS + 8 * wave + i] = v;
