@@ -210,15 +210,18 @@ __device__ __forceinline__ void load_node_operand(const ConvArgs& a, const TileC
   }
 }
 
+// The output channel of row m of output block b: with two blocks a lane's eight accumulators,
+// rows 4 g .. + 3 of both, are the channels 8 g .. + 7, 16 consecutive bytes of an activation.
+__host__ __device__ constexpr int out_channel(int cob, int b, int m) {
+  return cob == 2 ? 8 * (m >> 2) + 4 * b + (m & 3) : m;
+}
+
 // The ReLU mask of a tile's outputs in this lane: node xb 16 + px (the row's last node for
-// lanes past its end, which store nothing), channels 16 b + 4 g .. + 3.
-template <int COB>
-__device__ __forceinline__ void load_tile_mask(const ConvArgs& a, const TileCursor& tc, int px,
-                                               int g, uint2 (&mk)[COB]) {
+// lanes past its end, which store nothing), channels 8 g .. + 7.
+__device__ __forceinline__ uint4 load_tile_mask(const ConvArgs& a, const TileCursor& tc, int px,
+                                                int g) {
   const size_t opix = ((size_t)tc.n * a.H + tc.y) * a.W + min(tc.xb * 16 + px, a.W - 1);
-#pragma unroll
-  for (int b = 0; b < COB; ++b)
-    mk[b] = *reinterpret_cast<const uint2*>(a.mask + opix * 32 + 16 * b + 4 * g);
+  return *reinterpret_cast<const uint4*>(a.mask + opix * 32 + 8 * g);
 }
 
 template <int IN, int COB, int EPI>
@@ -237,13 +240,13 @@ void conv_kernel(ConvArgs a) {
   cur.set(t, a.xt, a.H);
   // the first tile's node operand is in flight while the weights are staged
   bf16x8 bf[KC];
-  uint2 mk[COB], mk2[COB];  // EPI_MASK: the ReLU masks of alternate tiles, loaded with their operands
+  uint4 mk, mk2;  // EPI_MASK: the ReLU masks of alternate tiles, loaded with their operands
   if (t < t_end) {
     load_node_operand<IN, KC>(a, cur, px, g, bf);
-    if constexpr (EPI == EPI_MASK) load_tile_mask<COB>(a, cur, px, g, mk);
+    if constexpr (EPI == EPI_MASK) mk = load_tile_mask(a, cur, px, g);
   }
   for (int i = threadIdx.x; i < KC * COB * 64; i += CONV_THREADS) sw[i] = a.w[i];
-  // this lane's biases (output channels 16 b + 4 g + i; the output layer's four in lanes
+  // this lane's biases (output channels 8 g + 4 b + i; the output layer's four in lanes
   // g = 0), held in registers: read per tile they would come after the tile's stores, and
   // waiting for them would wait for the next tile's operand loads too
   float bias[COB][4];
@@ -251,16 +254,16 @@ void conv_kernel(ConvArgs a) {
   for (int b = 0; b < COB; ++b)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      bias[b][i] = EPI == EPI_RELU ? a.bias[16 * b + 4 * g + i] : EPI == EPI_OUT ? a.bias[i] : 0.f;
+      bias[b][i] = EPI == EPI_RELU ? a.bias[8 * g + 4 * b + i] : EPI == EPI_OUT ? a.bias[i] : 0.f;
   __syncthreads();
   // one tile: its products, the next tile's operand and mask (into mnext), its epilogue (with
   // mnow).  The loop alternates the two mask registers, so no copy makes the epilogue wait for
   // the loads just issued.
-  auto tile_step = [&](const uint2 (&mnow)[COB], uint2 (&mnext)[COB]) {
+  auto tile_step = [&](const uint4& mnow, uint4& mnext) {
     const int y = cur.y, n = cur.n;
     const int x = cur.xb * 16 + px;
     const bool live = x < a.W;
-    // lane holds node x, output channels 16 b + 4 g + i
+    // lane holds node x, output channels 8 g + 4 b + i
     const size_t opix = ((size_t)n * a.H + y) * a.W + x;
     f32x4 acc[COB];
 #pragma unroll
@@ -286,7 +289,7 @@ void conv_kernel(ConvArgs a) {
     } else {
       load_node_operand<IN, KC>(a, next, px, g, bf);
     }
-    if constexpr (EPI == EPI_MASK) load_tile_mask<COB>(a, next, px, g, mnext);
+    if constexpr (EPI == EPI_MASK) mnext = load_tile_mask(a, next, px, g);
     cur = next;
     if (!live) return;
     if constexpr (EPI == EPI_OUT) {
@@ -299,24 +302,26 @@ void conv_kernel(ConvArgs a) {
         static_cast<float4*>(a.out)[opix] = o;
       }
     } else {
+      // 16 bytes per lane, 1 KB in a row per wavefront
+      const unsigned m4[4] = {mnow.x, mnow.y, mnow.z, mnow.w};
+      unsigned st[2 * COB];
 #pragma unroll
       for (int b = 0; b < COB; ++b) {
-        const int co = 16 * b + 4 * g;
         float v[4];
         if constexpr (EPI == EPI_RELU) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) v[i] = fmaxf(acc[b][i] + bias[b][i], 0.0f);
         } else {
-          const u16 m4[4] = {(u16)(mnow[b].x & 0xFFFF), (u16)(mnow[b].x >> 16),
-                             (u16)(mnow[b].y & 0xFFFF), (u16)(mnow[b].y >> 16)};
 #pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] = from_bf16(m4[i]) > 0.0f ? acc[b][i] : 0.0f;
+          for (int i = 0; i < 4; ++i)
+            v[i] = from_bf16((u16)(m4[2 * b + (i >> 1)] >> (16 * (i & 1)))) > 0.0f ? acc[b][i]
+                                                                                   : 0.0f;
         }
-        uint2 st;
-        st.x = (unsigned)to_bf16(v[0]) | ((unsigned)to_bf16(v[1]) << 16);
-        st.y = (unsigned)to_bf16(v[2]) | ((unsigned)to_bf16(v[3]) << 16);
-        *reinterpret_cast<uint2*>(static_cast<u16*>(a.out) + opix * 32 + co) = st;
+        st[2 * b] = (unsigned)to_bf16(v[0]) | ((unsigned)to_bf16(v[1]) << 16);
+        st[2 * b + 1] = (unsigned)to_bf16(v[2]) | ((unsigned)to_bf16(v[3]) << 16);
       }
+      *reinterpret_cast<uint4*>(static_cast<u16*>(a.out) + opix * 32 + 8 * g) =
+          make_uint4(st[0], st[1], st[2], st[3]);
     }
   };
   while (t < t_end) {
@@ -726,7 +731,7 @@ __global__ __launch_bounds__(256) void adam_kernel(AdamArgs a) {
 }
 
 // Fragment order of a weight operand: slot ((c * cob + b) * 64 + lane) * 8 + i holds the
-// weight of GEMM row 16 b + lane % 16 and product index k = 32 c + 8 (lane / 16) + i, where
+// weight of row out_channel(cob, b, lane % 16) and product index k = 32 c + 8 (lane / 16) + i, where
 // k is (tap c, channel k % 32) for 32-channel operands and (tap 4c + lane/16, channel i) for
 // 8-channel ones.  Forward: rows are output channels, W[row][tap][ch].  Input gradient: rows
 // are input channels, taps mirrored, W[ch][8 - tap][row].
@@ -746,7 +751,7 @@ __global__ __launch_bounds__(256) void frag_kernel(FragJobs jobs) {
   if (s >= a.slots) return;
   const int i = s & 7, lane = (s >> 3) & 63;
   const int b = (s >> 9) % a.cob, c = (s >> 9) / a.cob;
-  const int row = 16 * b + (lane & 15), g = lane >> 4;
+  const int row = out_channel(a.cob, b, lane & 15), g = lane >> 4;
   const int tap = a.wide ? c : 4 * c + g;
   const int ch = a.wide ? 8 * g + i : i;
   float v = 0.0f;
@@ -1036,7 +1041,7 @@ __device__ __forceinline__ void nt_layer(const NetArgs<T>& a, const bf16x8* sw, 
 #pragma unroll
       for (int b = 0; b < COB; ++b)
         acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[c][b], bf[c], acc[b], 0, 0, 0);
-    // lane holds node col of row i, output channels 16 b + 4 g + k
+    // lane holds node col of row i, output channels 8 g + 4 b + k
     if constexpr (LAST) {
       const int y = y0 + i, x = x0 + col;
       if (g == 0 && col < NT_W && y < a.H && x < a.W) {
@@ -1054,17 +1059,17 @@ __device__ __forceinline__ void nt_layer(const NetArgs<T>& a, const bf16x8* sw, 
         }
       }
     } else {
+      unsigned st[2 * COB];
 #pragma unroll
       for (int b = 0; b < COB; ++b) {
-        const int co = 16 * b + 4 * g;
         float v[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = fmaxf(acc[b][k] + bias[co + k], 0.0f);
-        uint2 st;
-        st.x = (unsigned)to_bf16(v[0]) | ((unsigned)to_bf16(v[1]) << 16);
-        st.y = (unsigned)to_bf16(v[2]) | ((unsigned)to_bf16(v[3]) << 16);
-        *reinterpret_cast<uint2*>(out + (size_t)(i * NT_PW + col) * 32 + co) = st;
+        for (int k = 0; k < 4; ++k) v[k] = fmaxf(acc[b][k] + bias[8 * g + 4 * b + k], 0.0f);
+        st[2 * b] = (unsigned)to_bf16(v[0]) | ((unsigned)to_bf16(v[1]) << 16);
+        st[2 * b + 1] = (unsigned)to_bf16(v[2]) | ((unsigned)to_bf16(v[3]) << 16);
       }
+      *reinterpret_cast<uint4*>(out + (size_t)(i * NT_PW + col) * 32 + 8 * g) =
+          make_uint4(st[0], st[1], st[2], st[3]);
     }
   }
 }
