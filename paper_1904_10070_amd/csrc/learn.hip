@@ -1003,15 +1003,20 @@ struct NetArgs {
   float s0, s1;
 };
 
-// One layer over the tile: rows `rows` of 16 NT_G-node groups, input plane `in` (features,
+// One layer over the tile: ROWS rows of NT_G 16-node groups, input plane `in` (features,
 // 8 channels, when IN8; else 32-channel activations), output plane `out` (32 channels) or,
-// for the last layer, the network output in HBM.
-template <bool IN8, int COB, bool LAST, typename T>
+// for the last layer, the network output in HBM.  A wavefront takes consecutive rows of one
+// group, so that a row's node operands, read from LDS once, serve the three rows that use them:
+// 1.1 MB of LDS reads per workgroup instead of 1.4.  128 x 320 nodes: 14.4 us (14.8 with rows dealt
+// out in turn); reading a layer's weights ahead of the barrier before it changes nothing.
+template <bool IN8, int COB, bool LAST, int ROWS, typename T>
 __device__ __forceinline__ void nt_layer(const NetArgs<T>& a, const bf16x8* sw, const void* in,
-                                         u16* out, int l, int rows, int y0, int x0,
-                                         double (&ps)[3]) {
+                                         u16* out, int l, int y0, int x0, double (&ps)[3]) {
   constexpr int KC = IN8 ? 3 : 9;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int PARTS = NT_WAVES / NT_G;              // wavefronts per group
+  constexpr int RPW = (ROWS + PARTS - 1) / PARTS;     // rows per wavefront
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int px = lane & 15, g = lane >> 4;
   bf16x8 wa[KC][COB];
 #pragma unroll
@@ -1019,19 +1024,25 @@ __device__ __forceinline__ void nt_layer(const NetArgs<T>& a, const bf16x8* sw, 
 #pragma unroll
     for (int b = 0; b < COB; ++b) wa[c][b] = sw[(c * COB + b) * 64 + lane];
   const float* bias = a.bias[l];
-  for (int u = wave; u < rows * NT_G; u += NT_WAVES) {
-    const int i = u / NT_G, col = (u % NT_G) * 16 + px;
-    bf16x8 bf[KC];
+  const int i0 = (wave / NT_G) * RPW, col = (wave % NT_G) * 16 + px;
+  bf16x8 bf[KC];
 #pragma unroll
-    for (int c = 0; c < KC; ++c) {
-      const int tap = IN8 ? 4 * c + g : c;
-      if (tap < 9) {
-        const int node = (i + tap / 3) * NT_PW + col + tap % 3;
-        bf[c] = IN8 ? static_cast<const bf16x8*>(in)[node]
-                    : static_cast<const bf16x8*>(in)[node * 4 + g];
-      } else {
-        bf[c] = zero_frag();
+  for (int r = 0; r < RPW; ++r) {
+    const int i = i0 + r;
+    if (i >= ROWS) break;
+    if constexpr (IN8) {
+#pragma unroll
+      for (int c = 0; c < KC; ++c) {
+        const int tap = 4 * c + g;
+        bf[c] = tap < 9 ? static_cast<const bf16x8*>(in)[(i + tap / 3) * NT_PW + col + tap % 3]
+                        : zero_frag();
       }
+    } else {  // chunk c = tap c = 3 dy + dx: the rows above are the last row's rows below
+#pragma unroll
+      for (int c = 0; c < KC; ++c)
+        bf[c] = r > 0 && c < 6 ? bf[(c + 3) % KC]
+                               : static_cast<const bf16x8*>(
+                                     in)[((i + c / 3) * NT_PW + col + c % 3) * 4 + g];
     }
     f32x4 acc[COB];
 #pragma unroll
@@ -1133,15 +1144,15 @@ __global__ __launch_bounds__(NT_THREADS) void net_step_kernel(NetArgs<T> a) {
   }
   __syncthreads();
   double ps[3] = {0.0, 0.0, 0.0};
-  nt_layer<true, 2, false>(a, sw + nt_frag_offset(0), sf, sa, 0, NT_H + 8, y0, x0, ps);
+  nt_layer<true, 2, false, NT_H + 8>(a, sw + nt_frag_offset(0), sf, sa, 0, y0, x0, ps);
   __syncthreads();
-  nt_layer<false, 2, false>(a, sw + nt_frag_offset(1), sa, sb, 1, NT_H + 6, y0, x0, ps);
+  nt_layer<false, 2, false, NT_H + 6>(a, sw + nt_frag_offset(1), sa, sb, 1, y0, x0, ps);
   __syncthreads();
-  nt_layer<false, 2, false>(a, sw + nt_frag_offset(2), sb, sa, 2, NT_H + 4, y0, x0, ps);
+  nt_layer<false, 2, false, NT_H + 4>(a, sw + nt_frag_offset(2), sb, sa, 2, y0, x0, ps);
   __syncthreads();
-  nt_layer<false, 2, false>(a, sw + nt_frag_offset(3), sa, sb, 3, NT_H + 2, y0, x0, ps);
+  nt_layer<false, 2, false, NT_H + 2>(a, sw + nt_frag_offset(3), sa, sb, 3, y0, x0, ps);
   __syncthreads();
-  nt_layer<false, 1, true>(a, sw + nt_frag_offset(4), sb, nullptr, 4, NT_H, y0, x0, ps);
+  nt_layer<false, 1, true, NT_H>(a, sw + nt_frag_offset(4), sb, nullptr, 4, y0, x0, ps);
   if (a.proj) {  // uniform: every thread takes part in the fixed-order block sums
     __shared__ double sh[NT_WAVES][3];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
