@@ -19,8 +19,9 @@
 //                             its operand; the next strip's loads are in flight during a
 //                             strip's products; per-workgroup partial sums are added in a
 //                             fixed order (FP64).
-// Grids are sized at network creation from the occupancy of each kernel: one wave of resident
-// workgroups where the per-workgroup set-up is large (weight gradient, 32-channel inputs).
+// Grids are sized at network creation: one wave of resident workgroups where the per-workgroup
+// set-up is large (32-channel inputs, from the kernels' occupancy; weight gradient, a fixed number
+// per compute unit).
 // Activations are bfloat16, channel-last [sample][theta][phi][channel].
 
 #include <hip/hip_runtime.h>
@@ -587,10 +588,9 @@ struct GradArgs {
 
 // GR_PARAMS parameters per block; each of the GR_PARTS half wavefronts sums every GR_PARTS-th
 // partial block of them, and their sums are added in a fixed order.  Bound by reading the partials
-// (28 MB for a 32 -> 32 layer), so the blocks have to reach every
-// compute unit: 289 for such a layer, 55 for the first (with 64 parameters each 145 and 28).
-// 2 x 128 x 169 nodes: 6.0 us on average over the layers (6.5); 16 x 128 x 320, a pass of eight
-// training steps 3043 us (3083).
+// (28 MB for a 32 -> 32 layer), so the blocks have to reach every compute unit: 289 for such a
+// layer, 55 for the first (with 64 parameters each 145 and 28).  2 x 128 x 169 nodes: 6.0 us on
+// average over the layers (6.5); 16 x 128 x 320, eight training steps 3043 us (3083).
 constexpr int GR_PARAMS = 32;  // 128 bytes of a partial block
 constexpr int GR_PARTS = 16;
 
