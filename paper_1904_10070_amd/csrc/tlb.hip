@@ -787,13 +787,15 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
       // issued after the last one's copy may be outstanding (in FP32 stages with y^n these
       // include the y^n loads)
       constexpr int m = k + PB - 1;
+      // WENO: the face stores and the reads of the last group's slots stay before the wait (which
+      // the compiler does not take for a memory access), the reads of the faces after the barrier
+      if constexpr (WENO) asm volatile("" ::: "memory");
       if constexpr (PF) {
         if (a.has_y0) wait_vm_lgkm0<ops_after_copy<D, DW, true, PB>(m, k)>();
         else wait_vm_lgkm0<ops_after_copy<D, DW, false, PB>(m, k)>();
       } else {
         wait_vm_lgkm0<ops_after_copy<D, DW, false, PB>(m, k)>();
       }
-      if constexpr (WENO) asm volatile("" ::: "memory");  // the face values stay on their side
       __builtin_amdgcn_s_barrier();
       if constexpr (WENO) asm volatile("" ::: "memory");
       // every wave is past populations k-PB .. k-1: their ring slots can be refilled
