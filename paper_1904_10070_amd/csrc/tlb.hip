@@ -3188,6 +3188,7 @@ int32_t tlb_autotune(tlb_grid* g, int32_t* rows) {
   clear_error();
   if (!g) return fail(TLB_EINVAL, "grid is NULL");
   if ((g->p.flags & (TLB_WENO5 | TLB_CH4)) || small_grid(g)) {  // one tile height only, or no tiles
+    TLB_HIP_CHECK(hipStreamSynchronize(g->stream));
     if (rows) *rows = g->ty;
     return TLB_OK;
   }
