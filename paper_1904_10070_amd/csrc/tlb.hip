@@ -525,20 +525,23 @@ __device__ __forceinline__ void ch_rhs(T phc, T inv_n, const RowCoef<T>& rc, con
 template <typename T, class M, class MP, class PF, class QF>
 __device__ __forceinline__ void ch4_rhs(T phc, T inv_n, const RowCoef<T>& rc, const Consts<T>& c,
                                         M m, MP mp, PF P, QF Q, T& Xth, T& Fph, T& Lphi) {
+  TLB_EXPLICIT_FMA
   auto G = [&](int o) {  // face gradient numerator at the face (q + o) + 1/2
-    return m(o - 1) - T(27) * m(o) + T(27) * m(o + 1) - m(o + 2);
+    TLB_EXPLICIT_FMA
+    return fused(T(27), m(o + 1), fused(T(-27), m(o), m(o - 1))) - m(o + 2);
   };
-  const T dmu_th = (m(-2) - T(8) * m(-1)) + (T(8) * m(1) - m(2));
-  const T dmu_ph = (mp(-2) - T(8) * mp(-1)) + (T(8) * mp(1) - mp(2));
-  Xth = phc * dmu_th * c.inv_12rdth;
-  Fph = -phc * dmu_ph * rc.inv_12Jdph * inv_n;
-  const T lap_th = rc.l4[0] * G(-2) - T(27) * (rc.l4[1] * G(-1)) + T(27) * (rc.l4[2] * G(0)) -
-                   rc.l4[3] * G(1);
-  const T lap_ph = rc.lp4 * ((-mp(-2) + T(16) * mp(-1)) - T(30) * mp(0) + (T(16) * mp(1) - mp(2)));
-  Lphi = c.M * (lap_th + lap_ph);
-  if (c.ch_adv)
-    Lphi -= ((P(-2) - T(8) * P(-1)) + (T(8) * P(1) - P(2))) * rc.inv_12rJdth +
-            ((Q(-2) - T(8) * Q(-1)) + (T(8) * Q(1) - Q(2))) * rc.inv_12Jdph;
+  auto central = [&](auto h) {  // 12 times the spacing times the central difference
+    TLB_EXPLICIT_FMA
+    return fused(T(-8), h(-1), h(-2)) + fused(T(8), h(1), -h(2));
+  };
+  Xth = phc * central(m) * c.inv_12rdth;
+  Fph = -phc * central(mp) * rc.inv_12Jdph * inv_n;
+  const T lap_th = fused(-rc.l4[3], G(1),
+                         fused(T(27), rc.l4[2] * G(0),
+                               fused(rc.l4[0], G(-2), T(-27) * (rc.l4[1] * G(-1)))));
+  const T lap_ph = fused(T(-30), mp(0), fused(T(16), mp(-1), -mp(-2))) + fused(T(16), mp(1), -mp(2));
+  Lphi = c.M * fused(rc.lp4, lap_ph, lap_th);
+  if (c.ch_adv) Lphi = Lphi - products(central(P), rc.inv_12rJdth, central(Q), rc.inv_12Jdph);
 }
 
 // Runge-Kutta combine of the order parameter: own = its stored value at the stage input (FP32: the
