@@ -1842,7 +1842,7 @@ __global__ __launch_bounds__(RED_THREADS) void tlb_fft_rows_kernel(const T* phi,
   }
 }
 
-// the direct sum for rows too long for two copies in LDS, one block per row
+// the direct sum, one block per row: for rows too long for two copies in LDS or of prime length
 template <typename T>
 __global__ __launch_bounds__(RED_THREADS) void tlb_dft_rows_kernel(const T* phi, const T* phib,
                                                                   const double2* tw, double2* X,
@@ -2819,9 +2819,16 @@ hipError_t structure_launch(const tlb_grid* g, void* base, bool twiddles, double
   if (twiddles)
     hipLaunchKernelGGL(tlb_twiddle_kernel, dim3((np + nt + RED_THREADS - 1) / RED_THREADS),
                        dim3(RED_THREADS), 0, g->stream, tw, np, nt);
-  if (np <= FFT_MAX)
+  const FftPlan rows = fft_plan(np);
+  // Rows of prime length have nothing to factor: one pass of np complex terms for np values per two
+  // rows is twice the arithmetic of the direct sum of real terms for the np / 2 + 1 modes, in half
+  // the blocks.  Whole calls in us, FFT / direct: 61 x 127 43 / 35, 512 x 1009 383 / 300, 127 x
+  // 4093 8680 / 2990, 3 x 5119 13300 / 3810.  (One factor of two to split off is enough for the FFT
+  // on many rows: 640 x 1594 781, where 640 x 1597 takes 1108 directly.)
+  const bool prime = rows.stages == 1 && rows.radix[0] > 8;
+  if (np <= FFT_MAX && !prime)
     hipLaunchKernelGGL(tlb_fft_rows_kernel<T>, dim3((nt + 1) / 2), dim3(RED_THREADS),
-                       2 * np * sizeof(double2), g->stream, phi, phib, tw, X, nt, fft_plan(np));
+                       2 * np * sizeof(double2), g->stream, phi, phib, tw, X, nt, rows);
   else
     hipLaunchKernelGGL(tlb_dft_rows_kernel<T>, dim3(nt), dim3(RED_THREADS), np * sizeof(double),
                        g->stream, phi, phib, tw, X, nt, np);
