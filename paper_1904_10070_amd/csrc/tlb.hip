@@ -2805,15 +2805,15 @@ size_t dft_bytes(int nt, int np) {
 constexpr int FFT_MAX = 5120;
 static_assert(2 * FFT_MAX * sizeof(double2) <= 160 * 1024, "two copies in LDS");
 
-// the transforms and sums of grid g's phi in the workspace at `base` (dft_bytes); the three results
-// follow the partials.  Twiddle factors are made first if `twiddles`.
+// the transforms of grid g's phi and their sums per mode in the workspace at `base` (dft_bytes).
+// Twiddle factors are made first if `twiddles`.
 template <typename T>
-hipError_t structure_launch(const tlb_grid* g, void* base, bool twiddles, double** result) {
+hipError_t structure_launch(const tlb_grid* g, void* base, bool twiddles, double** partials) {
   const int nt = g->p.n_theta, np = g->p.n_phi, nm = np / 2 + 1;
   double2* X = static_cast<double2*>(base);
   double2* tw = X + (size_t)nm * nt;
   double* part = reinterpret_cast<double*>(tw + np + nt);
-  *result = part + 2 * nm;
+  *partials = part;
   const T* phi = static_cast<const T*>(g->phi[0]);
   const T* phib = reinterpret_cast<const T*>(g->phi_base);
   if (twiddles)
@@ -2834,14 +2834,32 @@ hipError_t structure_launch(const tlb_grid* g, void* base, bool twiddles, double
                        g->stream, phi, phib, tw, X, nt, np);
   hipLaunchKernelGGL(tlb_fft_cols_kernel, dim3(nm), dim3(RED_THREADS), 2 * nt * sizeof(double2),
                      g->stream, X, tw + np, np, g->p.r, g->p.R, part, fft_plan(nt));
-  hipLaunchKernelGGL(tlb_structure_final_kernel, dim3(1), dim3(RED_THREADS), 0, g->stream, part,
-                     nm, *result);
   return hipGetLastError();
 }
 
-// 64 KB of LDS per block, the limit on rows of doubles and columns of complex doubles
+// the longest rows (direct sums from 64 KB of LDS) and columns (two complex copies in 128 KB)
+constexpr int STRUCTURE_MAX_ROW = 8192, STRUCTURE_MAX_COLUMN = 4096;
 bool structure_size_ok(int nt, int np) {
-  return (size_t)np * sizeof(double) <= 64 * 1024 && (size_t)nt * sizeof(double2) <= 64 * 1024;
+  return np <= STRUCTURE_MAX_ROW && nt <= STRUCTURE_MAX_COLUMN;
+}
+
+// tlb_structure_final_kernel on the host, in the same order: the copy of the partial sums takes no
+// longer than that of the results, and a launch less is 3 us of a call (24 of 27 for the smallest
+// grids).
+void structure_final(const double* part, int nm, double out[3]) {
+  double sum[2] = {0.0, 0.0};
+  for (int c = 0; c < 2; ++c)
+    for (int w = 0; w < RED_THREADS / 64; ++w) {
+      double v[64] = {};
+      for (int lane = 0; lane < 64; ++lane)
+        for (int m = 64 * w + lane; m < nm; m += RED_THREADS) v[lane] += part[2 * m + c];
+      for (int d = 32; d >= 1; d >>= 1)
+        for (int lane = 0; lane < d; ++lane) v[lane] += v[lane + d];
+      sum[c] += v[0];
+    }
+  out[0] = sum[1] > 0.0 ? 2.0 * M_PI * sum[0] / sum[1] : INFINITY;
+  out[1] = sum[0];
+  out[2] = sum[1];
 }
 
 template <typename T>
@@ -2857,8 +2875,8 @@ int32_t structure_t(tlb_grid* g, double out[3]) {
       return fail(TLB_ENOMEM, std::string("structure factor workspace: ") + hipGetErrorString(e));
     }
   }
-  double* res = nullptr;
-  hipError_t e = structure_launch<T>(g, g->dft_work, first, &res);
+  double* part = nullptr;
+  hipError_t e = structure_launch<T>(g, g->dft_work, first, &part);
   if (e != hipSuccess) {
     if (first) {  // the twiddle factors may not have been made
       (void)hipFree(g->dft_work);
@@ -2866,8 +2884,12 @@ int32_t structure_t(tlb_grid* g, double out[3]) {
     }
     return fail(TLB_EHIP, std::string("structure factor: ") + hipGetErrorString(e));
   }
-  TLB_HIP_CHECK(hipMemcpyAsync(out, res, 3 * sizeof(double), hipMemcpyDeviceToHost, g->stream));
+  const int nm = np / 2 + 1;
+  double h[2 * (STRUCTURE_MAX_ROW / 2 + 1)];
+  TLB_HIP_CHECK(
+      hipMemcpyAsync(h, part, 2 * nm * sizeof(double), hipMemcpyDeviceToHost, g->stream));
   TLB_HIP_CHECK(hipStreamSynchronize(g->stream));
+  structure_final(h, nm, out);
   return TLB_OK;
 }
 
@@ -2922,8 +2944,16 @@ int32_t structure_noalloc_t(tlb_grid* g, double out[3]) {
   void* base = nullptr;
   int32_t rc = scratch_address(&base);
   if (rc != TLB_OK) return rc;
-  double* res = nullptr;
-  if (structure_launch<T>(g, base, true, &res) != hipSuccess)
+  const int nm = np / 2 + 1;
+  double* part = nullptr;
+  hipError_t e = structure_launch<T>(g, base, true, &part);
+  double* res = part + 2 * nm;
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(tlb_structure_final_kernel, dim3(1), dim3(RED_THREADS), 0, g->stream, part,
+                       nm, res);
+    e = hipGetLastError();
+  }
+  if (e != hipSuccess)
     return fail_static(TLB_EHIP, "structure factor (no allocation): kernel launch failed");
   if (hipMemcpyAsync(out, res, 3 * sizeof(double), hipMemcpyDeviceToHost, g->stream) !=
           hipSuccess ||
