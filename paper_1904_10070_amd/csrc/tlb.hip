@@ -1670,7 +1670,7 @@ __global__ __launch_bounds__(RED_THREADS) void tlb_diag_kernel(const T* f, const
 // of phi need not be removed.  tw holds exp(-2 pi i j / n) for the row length n_phi followed by
 // the column length n_theta.  Bound by latency: a few LDS passes per row pair or column.  512 x
 // 1280: 15.6 + 9.9 us for rows and columns, where the direct O(n^2) sums took 900 + 323 us.
-constexpr int FFT_STAGES = 16;
+constexpr int FFT_STAGES = 8;
 struct FftPlan {
   int n, stages;
   int radix[FFT_STAGES];
@@ -1693,7 +1693,7 @@ FftPlan fft_plan(int n) {
       m /= r;
     }
   }
-  return p;  // n < 8^16: at most FFT_STAGES factors for every n of the kernels below
+  return p;  // n <= 8192: at most FFT_STAGES factors (4374 = 2 3^7 has the most)
 }
 
 __device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
@@ -2866,7 +2866,7 @@ template <typename T>
 int32_t structure_t(tlb_grid* g, double out[3]) {
   const int nt = g->p.n_theta, np = g->p.n_phi;
   if (!structure_size_ok(nt, np))
-    return fail(TLB_EINVAL, "structure factor: a row or column exceeds the 64 KB of LDS per block");
+    return fail(TLB_EINVAL, "structure factor: rows of more than 8192 or columns of more than 4096 nodes");
   const bool first = !g->dft_work;
   if (first) {
     hipError_t e = hipMalloc(&g->dft_work, dft_bytes(nt, np));
@@ -2936,7 +2936,7 @@ int32_t structure_noalloc_t(tlb_grid* g, double out[3]) {
   const int nt = g->p.n_theta, np = g->p.n_phi;
   if (!structure_size_ok(nt, np))
     return fail_static(TLB_EINVAL,
-                       "structure factor: a row or column exceeds the 64 KB of LDS per block");
+                       "structure factor: rows of more than 8192 or columns of more than 4096 nodes");
   if (scratch_need(nt, np) > SCRATCH_BYTES)
     return fail_static(TLB_EINVAL,
                        "structure factor (no allocation): grid too large for the 24 MiB "
