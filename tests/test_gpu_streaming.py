@@ -1,0 +1,70 @@
+"""Streaming accesses (levels 0, 1 and 2 by the size of the state copies) do not change bits.  A grid
+is stepped alone, in a batch with a second one of its shape (twice the size, so another level) and in
+a batch with a torus whose rows have no 16-byte copies (level 0 for all).  State copies in MB and
+levels alone / with its like: FP64 320 x 1280 167 / 334 (0 / 1), 640 x 1280 334 / 668 (1 / 2), 960 x
+1280 501 / 1003 (1 / 2); FP32 768 x 1536 241 / 481 (0 / 2), 1408 x 1600 460 / 919 (2 / 2).  One FP64
+grid of level 1 is also compared with the oracle, to 1e-12 as in the other parity tests."""
+import numpy as np
+import pytest
+
+from paper_1904_10070_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def params(shape):
+    p = inputs.params_three_cells(1.0, 2.5, shape[0], shape[1], A=0.5, M=2.5e-3, tau=0.6, dt=1.0)
+    return p.with_(dt=0.25 * inputs.stable_dt(p))
+
+
+def make(shape, precision, density=1.0, seed=8):
+    from paper_1904_10070_amd import TorusGrid
+    p = params(shape)
+    phi, n, ut, up = inputs.random_state(p, seed=seed)
+    g = TorusGrid(p, precision=precision)
+    g.set_state(phi, density * n, ut, up)
+    return g
+
+
+@pytest.mark.parametrize("precision, density, shape", [(64, 1.0, (320, 1280)), (64, 1.0, (640, 1280)),
+                                                       (64, 1.0, (960, 1280)), (32, 1.0, (768, 1536)),
+                                                       (32, 20.0, (1408, 1600))])
+def test_levels_do_not_change_results(torch_cuda, precision, density, shape):
+    from paper_1904_10070_amd import TorusBatch
+    first = None
+    for rows in (4, 8, 16):
+        g = make(shape, precision, density)
+        g.set_tile_rows(rows)
+        g.step(3)
+        state = g.get_state()
+        g.close()
+        first = first or state
+        for a, b in zip(first, state):
+            assert torch_cuda.equal(a, b), rows
+    for other in (shape, (16, 61)):
+        g, h = make(shape, precision, density), make(other, precision, density, seed=9)
+        batch = TorusBatch([h, g])
+        batch.step(3)
+        for a, b in zip(first, g.get_state()):
+            assert torch_cuda.equal(a, b), other
+        batch.close()
+        g.close()
+        h.close()
+
+
+def test_level_one_matches_oracle(torch_cuda):
+    from oracle import ref
+    shape = (640, 1280)
+    g = make(shape, 64)
+    g.step(2)
+    f, phi = (x.cpu().numpy() for x in g.get_state())
+    p = params(shape)
+    o = ref.RefGrid(**p.as_dict())
+    o.set_state(*inputs.random_state(p, seed=8))
+    o.step(2)
+    f_ref, phi_ref = o.get_state()
+    ef = np.abs(f - f_ref).max() / np.abs(f_ref).max()
+    ep = np.abs(phi - phi_ref).max() / np.abs(phi_ref).max()
+    print(f"{ef:.1e} {ep:.1e}", flush=True)
+    assert ef <= 1e-12 and ep <= 1e-12
+    g.close()
