@@ -34,9 +34,10 @@
  * Arithmetic in precision 32 differs from precision 64 in two places beyond the element type:
  * 1/n is the hardware reciprocal (1 ulp), and the Runge-Kutta combination of phi is taken on
  * the deviations as d^n + b (d_s - d^n + dt L) rather than (1 - b) phi^n + b (phi_s + dt L)
- * (the same value).  Grids whose three state copies exceed the last-level cache by enough (430 MB in
- * precision 32, 300 MB in precision 64) write their stage outputs with streaming (nontemporal)
- * stores.
+ * (the same value).  Grids whose three state copies exceed the last-level cache by enough (430 MB
+ * in precision 32, 300 MB in precision 64) and whose rows are whole 64-byte lines write their stage
+ * outputs with streaming (nontemporal) stores; in precision 64 other rows of an even number of
+ * nodes do from 300 to 900 MB.  TLB_WENO5 and TLB_CH4 grids do not.  The results are the same.
  *
  * Ownership.  The caller allocates and owns every buffer passed in (state buffers, moment
  * buffers); they must outlive the grid handle.  The library owns its per-row geometry table,
@@ -251,8 +252,9 @@ int32_t tlb_autotune(tlb_grid* grid, int32_t* rows);
  * Each grid ends exactly (bit for bit) where tlb_step_n on it alone would.  The batch
  * keeps pointers to the grids, which must outlive it and must not be stepped on their own
  * between batch calls on different streams.  All grids must have the same precision.
- * Ensembles whose state copies together are as large as those of such grids use streaming
- * (nontemporal) accesses as they do; the results are the same.
+ * Ensembles whose state copies together are as large as those of grids with streaming
+ * (nontemporal) accesses use them too, by the rows of at least two thirds of their nodes, unless a
+ * torus has rows that are no multiple of 16 bytes; the results are the same.
  * Errors: TLB_EINVAL (NULL, empty, mixed precision, duplicate), TLB_ENOMEM, TLB_EHIP.      */
 typedef struct tlb_batch tlb_batch;
 int32_t tlb_create_batch(tlb_grid* const* grids, int32_t n_grids, void* hip_stream,

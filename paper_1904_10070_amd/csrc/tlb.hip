@@ -2046,7 +2046,8 @@ const void* stage_fn_ty(int ty) {
     default: return reinterpret_cast<const void*>(&tlb_stage_kernel<T, VEC, 8, false, STREAM, GENREF>);
   }
 }
-// streaming: the 16-byte-copy form only (large grids have n_phi % 4 == 0); FP32 has levels 0 and 2
+// streaming: the 16-byte-copy form only (in FP32 rows of whole lines have it; FP64 rows of an odd
+// number of nodes stay at level 0); FP32 has levels 0 and 2
 template <typename T, bool VEC, bool GENREF>
 const void* stage_fn_stream(int ty, int level) {
   if constexpr (VEC) {
@@ -2063,19 +2064,28 @@ bool general_reference(const tlb_grid* g) {
   return stores_deviation<T>() && g->n_ref != 1.0;
 }
 
+// Rows of whole 64-byte lines, where streaming stores write whole lines wherever a row begins
+bool whole_lines(const tlb_grid* g) { return (size_t)g->p.n_phi * g->elem % 64 == 0; }
+
 // The streaming level of grids (or ensembles) whose three state copies, 51 values per node, take
-// `bytes`.  Times per step in us at levels 0 / 1 / 2.  FP64: 267 MB 137 / 149 / 170, 334 MB 215 / 190
-// / 219, 522 MB 348 / 310 / 318, 668 MB 450 / 431 / 426, 1069 MB 704 / 688 / 673.  FP32: 334 MB
-// 200 / 206 / 209, 427 MB 270 / 268 / 270, 534 MB 356 / 333 / 332, 835 MB 539 / 528 / 513 (1 GiB was
-// the line before).
-int streaming_level(double bytes, size_t elem) {
-  if (elem == 4) return bytes > 430e6 ? 2 : 0;
+// `bytes`, with rows of whole 64-byte lines (`lines`) or not.  Times per step in us at levels
+// 0 / 1 / 2.
+// FP64, whole lines: 267 MB 137 / 149 / 170, 334 MB 215 / 190 / 219, 522 MB 348 / 310 / 318, 668 MB
+// 450 / 431 / 426, 1069 MB 704 / 688 / 673.
+// FP32, whole lines: 334 MB 200 / 206 / 209, 427 MB 270 / 268 / 270, 534 MB 356 / 333 / 332, 835 MB
+// 539 / 528 / 513, 2132 MB (lines of 64, not of 128 bytes) 1391 / 1341 / 1328.
+// Other rows begin and end inside lines, which streaming stores write in parts.  FP64: 335 MB 227 / 198
+// / 245, 624 MB 424 / 407 / 430, 818 MB 530 / 527 / 535, 980 MB 633 / 636 / 644, 1634 MB 1026 / 1046 /
+// 1058.  FP32: 465 MB 307 / 306 / 335, 665 MB 467 / 486 / 513, 2131 MB 1436 / 1529 / 1617.
+int streaming_level(double bytes, size_t elem, bool lines) {
+  if (elem == 4) return lines && bytes > 430e6 ? 2 : 0;
+  if (!lines) return bytes > 300e6 && bytes < 900e6 ? 1 : 0;
   return bytes > 600e6 ? 2 : bytes > 300e6 ? 1 : 0;
 }
 double state_bytes(const tlb_grid* g) {
   return 51.0 * g->p.n_theta * (double)g->p.n_phi * (double)g->elem;
 }
-int streaming(const tlb_grid* g) { return streaming_level(state_bytes(g), g->elem); }
+int streaming(const tlb_grid* g) { return streaming_level(state_bytes(g), g->elem, whole_lines(g)); }
 
 // The small-grid kernel runs grids of at most this many 64-node row segments (not WENO-5, whose
 // arithmetic outweighs the latencies).  Times per step in us, tiles / small-grid kernel: FP32, 960
@@ -3267,14 +3277,16 @@ int32_t tlb_create_batch(tlb_grid* const* grids, int32_t n, void* hip_stream, tl
   b->ty = DEFAULT_TY;
   b->stream = static_cast<hipStream_t>(hip_stream);
   b->vec = true;
-  double bytes = 0.0;
+  double bytes = 0.0, whole = 0.0;
   for (int i = 0; i < n; ++i) {
     b->grids[i] = grids[i];
     b->vec = b->vec && (b->precision == 64 ? vec_ok<double>(grids[i]->p.n_phi)
                                            : vec_ok<float>(grids[i]->p.n_phi));
     bytes += state_bytes(grids[i]);
+    if (whole_lines(grids[i])) whole += state_bytes(grids[i]);
   }
-  b->streaming = streaming_level(bytes, grids[0]->elem);
+  // (streaming costs tori without whole lines about twice what it gains the others)
+  b->streaming = streaming_level(bytes, grids[0]->elem, 3.0 * whole >= 2.0 * bytes);
   const size_t args_bytes = b->precision == 64 ? sizeof(StageArgs<double>) : sizeof(StageArgs<float>);
   hipError_t e = hipMalloc(&b->table, args_bytes * 3 * n);
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&b->tile_begin), sizeof(int) * (n + 1));

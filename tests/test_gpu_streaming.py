@@ -2,8 +2,10 @@
 is stepped alone, in a batch with a second one of its shape (twice the size, so another level) and in
 a batch with a torus whose rows have no 16-byte copies (level 0 for all).  State copies in MB and
 levels alone / with its like: FP64 320 x 1280 167 / 334 (0 / 1), 640 x 1280 334 / 668 (1 / 2), 960 x
-1280 501 / 1003 (1 / 2); FP32 768 x 1536 241 / 481 (0 / 2), 1408 x 1600 460 / 919 (2 / 2).  One FP64
-grid of level 1 is also compared with the oracle, to 1e-12 as in the other parity tests."""
+1280 501 / 1003 (1 / 2); FP32 768 x 1536 241 / 481 (0 / 2), 1408 x 1600 460 / 919 (2 / 2).  Rows that
+are not whole 64-byte lines have lines of their own: FP64 640 x 1250 326 / 653 (1 / 1), 900 x 1250
+459 / 918 (1 / 0), FP32 1200 x 1900 465 / 930 (0 / 0).  One FP64 grid of level 1 is also compared with
+the oracle, to 1e-12 as in the other parity tests."""
 import numpy as np
 import pytest
 
@@ -28,7 +30,9 @@ def make(shape, precision, density=1.0, seed=8):
 
 @pytest.mark.parametrize("precision, density, shape", [(64, 1.0, (320, 1280)), (64, 1.0, (640, 1280)),
                                                        (64, 1.0, (960, 1280)), (32, 1.0, (768, 1536)),
-                                                       (32, 20.0, (1408, 1600))])
+                                                       (32, 20.0, (1408, 1600)),
+                                                       (64, 1.0, (640, 1250)), (64, 1.0, (900, 1250)),
+                                                       (32, 1.0, (1200, 1900))])
 def test_levels_do_not_change_results(torch_cuda, precision, density, shape):
     from paper_1904_10070_amd import TorusBatch
     first = None
