@@ -31,9 +31,10 @@
  * (error-free two-sum), so a state's bits do not depend on how its steps were split into
  * calls or checked runs.  tlb_set_state, tlb_get_state, tlb_get_moments and the diagnostics convert; a
  * caller reading an FP32 grid's phi buffers directly sees deviations.
- * Arithmetic in precision 32 differs from precision 64 in two places beyond the element type:
- * 1/n is the hardware reciprocal (1 ulp), and the Runge-Kutta combination of phi is taken on
- * the deviations as d^n + b (d_s - d^n + dt L) rather than (1 - b) phi^n + b (phi_s + dt L)
+ * Arithmetic in precision 32 differs from precision 64 in three places beyond the element type:
+ * 1/n is the hardware reciprocal (1 ulp), so are the reciprocals that weight the candidates of
+ * TLB_WENO5, and the Runge-Kutta combination of phi is taken on the deviations as
+ * d^n + b (d_s - d^n + dt L) rather than (1 - b) phi^n + b (phi_s + dt L)
  * (the same value).  Grids whose three state copies exceed the last-level cache by enough (430 MB
  * in precision 32, 300 MB in precision 64) and whose rows are whole 64-byte lines write their stage
  * outputs with streaming (nontemporal) stores; in precision 64 other rows of an even number of
@@ -220,7 +221,8 @@ int32_t tlb_diagnostics(tlb_grid* grid, double out[2], double* phi_avg, double* 
 int32_t tlb_structure_length(tlb_grid* grid, double out[3]);
 
 /* tlb_structure_length without any allocation, for callers that cannot allocate device
- * memory (serving loops, code that must not call hipMalloc): the same outputs from a workspace that is a static device array of 24 MiB per GPU, held from the
+ * memory (serving loops, code that must not call hipMalloc): the same outputs from a workspace
+ * that is a static device array of 24 MiB per GPU, held from the
  * library's first use on that GPU until the process ends; nothing is allocated, on the device
  * or the host.  Grids may need (n_theta n_phi + n_theta + n_phi) 16 + 16 n_phi + 24 bytes of it
  * (up to about 1.5 M nodes); larger grids get TLB_EINVAL.  Every call on one GPU uses the same
