@@ -337,9 +337,16 @@ void conv_kernel(ConvArgs a) {
 // weight gradient: dW[o][t][i] = sum over nodes of e[node][o] a[node + offset(t)][i]
 
 constexpr int WG_THREADS = 256;
-// workgroups per compute unit: as many as one wave of resident workgroups of each kernel's first
-// form; the number fixes the order of the gradient's sums, so it stays
-constexpr int wgrad_per_cu(int cis) { return cis == 8 ? 5 : 3; }
+// Workgroups per compute unit, and with them the order of the gradient's sums: as many as were
+// resident of the kernels that transposed their tiles into LDS, so that trained weights keep their
+// bits.  (More would be resident, but each writes its partial gradient and grad_reduce_kernel reads
+// it: 28 MB at three per unit of a 32 -> 32 layer.  Five of the first layer's, whose partial
+// gradients are a quarter as large, take as long as four: 375 us per training step of 16 x 128 x 320
+// nodes.)
+constexpr int wgrad_per_cu(int cis) { return cis == 8 ? 4 : 3; }
+// wavefronts per SIMD that the registers have to allow (with four for the first layer, a training step
+// of one strip takes 106 us instead of 104.5)
+constexpr int wgrad_waves(int cis) { return cis == 8 ? 5 : 3; }
 
 struct WgradArgs {
   const u16* e;        // error signal bf16 [n][H][W][COS]
@@ -478,7 +485,7 @@ struct WgradStrip {
 };
 
 template <int CIS, int COS>
-__global__ __launch_bounds__(WG_THREADS) __attribute__((amdgpu_waves_per_eu(wgrad_per_cu(CIS))))
+__global__ __launch_bounds__(WG_THREADS) __attribute__((amdgpu_waves_per_eu(wgrad_waves(CIS))))
 void wgrad_kernel(WgradArgs a) {
   constexpr int CIB = (CIS + 15) / 16, COB = (COS + 15) / 16;
   // 16 x 16 output fragments (tap t, output block bc, input block bi); a wavefront takes
@@ -1807,9 +1814,7 @@ int32_t tlb_cnn_create(const tlb_cnn_desc* desc, void* hip_stream, tlb_cnn** out
       net->conv_grid[v] = (int)std::min<long long>(CONV_MAX_BLOCKS,
                                                    (long long)std::max(resident, 1) * cus);
   }
-  // Weight-gradient grids, each workgroup taking consecutive strips: three per compute unit, five
-  // for the first layer, whose partial gradients are a quarter as large.  (More would be resident,
-  // but each writes its partial gradient and grad_reduce_kernel reads it: 28 MB at three per unit.)
+  // weight-gradient grids, each workgroup taking consecutive strips
   for (int l = 0; l < NL; ++l) net->wgrad_grid[l] = std::min(WG_MAX_BLOCKS, wgrad_per_cu(L_CIS[l]) * cus);
   if (e != hipSuccess) {
     free_net(net);
