@@ -408,8 +408,8 @@ __device__ __forceinline__ bf16x8 node_operand(const u16* tile, int j0, int ch0,
 // the input rows in a ring of four, so that the next strip is stored while others still read: one
 // barrier per strip instead of two.
 //
-// 16 x 128 x 320 nodes: 32 -> 32 channels 25.3 us (32.5 with the transposed tiles), 32 -> 4 19.2
-// (26.5), 6 -> 32 17.1 (20.3).  The 32 -> 32 layer moves 112 MB (activations 42, errors 42, the
+// 16 x 128 x 320 nodes: 32 -> 32 channels 22.9 us (30.8 with the transposed tiles), 32 -> 4 17.8
+// (25.2), 6 -> 32 16.1 (19.6).  The 32 -> 32 layer moves 112 MB (activations 42, errors 42, the
 // partial sums of 768 workgroups 28), 17 us at the rate of a large copy; the rest is the
 // workgroups' start and end, 13 strips apart.  Loads two strips ahead gave nothing: more
 // registers, fewer wavefronts.
@@ -494,10 +494,12 @@ void wgrad_kernel(WgradArgs a) {
   constexpr int PPW = (NP + 3) / 4;      // pairs per wavefront
   using Strip = WgradStrip<CIS, COS>;
   __shared__ __attribute__((aligned(16))) u16 sE[2 * Strip::ERR];
-  // four rows; in the end the error's sums per node and channel (floats)
-  constexpr int SB = COS + 1;  // floats per node: an odd pitch spreads a channel over the banks
-  constexpr int SA = 4 * Strip::ROW > 128 * SB ? 4 * Strip::ROW : 128 * SB;
-  __shared__ __attribute__((aligned(16))) u16 sA[SA];
+  __shared__ __attribute__((aligned(16))) u16 sA[4 * Strip::ROW];
+  // the error's sums per node and channel; an odd pitch spreads a channel over the banks.  (Beside the
+  // rows, not in their place: written before the last strip's products they cost no barriers of their
+  // own, 24.3 us otherwise for 32 -> 32 channels and 5.0 instead of 4.7 for a single strip.)
+  constexpr int SB = COS + 1;
+  __shared__ float sB[64 * SB];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3;
   const int px = lane & 15, g = lane >> 4;
@@ -543,13 +545,30 @@ void wgrad_kernel(WgradArgs a) {
     }
     st.store(a, pos, E, sA, bsum);
     nxt = pos;
-    if (s + 1 < s1) nxt.next(a.xs, a.H);
-    st.load(a, nxt);
+    if (s + 1 < s1) {
+      nxt.next(a.xs, a.H);
+      st.load(a, nxt);
+    } else if (threadIdx.x < Strip::NE) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        sB[(threadIdx.x / Strip::CE) * SB + 8 * (threadIdx.x % Strip::CE) + i] = bsum[i];
+    }
     __syncthreads();
     products(E, pos.y);
     pos = nxt;
   }
   float* out = a.partial + (size_t)blockIdx.x * (COS * 9 * CIS + COS);
+  // bias gradient: a thread's sums belong to node tid / CE and channels 8 (tid % CE) .. + 7; wavefront
+  // w adds channels 8 w .. + 7 over the 64 nodes, a lane each
+  if (threadIdx.x < Strip::NE) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      float v = sB[lane * SB + 8 * wave + i];
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+      if (lane == 0) out[COS * 9 * CIS + 8 * wave + i] = v;
+    }
+  }
 #pragma unroll
   for (int k = 0; k < PPW; ++k) {
     const int pr = wave + 4 * k;
@@ -563,24 +582,6 @@ void wgrad_kernel(WgradArgs a) {
           const int co = 16 * bc + 4 * g + i;
           if (co < COS && ci < CIS) out[(co * 9 + t) * CIS + ci] = acc[k][bc][i];
         }
-    }
-  }
-  // bias gradient: a thread's sums belong to node tid / CE and channels 8 (tid % CE) .. + 7; wavefront
-  // w adds channels 8 w .. + 7 over the 64 nodes, a lane each
-  __syncthreads();
-  float* sB = reinterpret_cast<float*>(sA);  // [64][SB]
-  if (threadIdx.x < Strip::NE)
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      sB[(threadIdx.x / Strip::CE) * SB + 8 * (threadIdx.x % Strip::CE) + i] = bsum[i];
-  __syncthreads();
-  if (threadIdx.x < Strip::NE) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      float v = sB[lane * SB + 8 * wave + i];
-#pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-      if (lane == 0) out[COS * 9 * CIS + 8 * wave + i] = v;
     }
   }
 }
