@@ -847,18 +847,18 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const int tx, 
         sFaceP[h][p][lx * (TX + 1)] = weno_face<T, j >= 2>([&](int o) { return e[o]; });
       }
     } else {
-    dph = uw5_difference<T, j >= 2>([&](int o) { return buf[cN + o]; });
-    // theta direction: sum_o uw5(o) J_{q+o} / (r J_q dtheta) f_{q+o}
-    constexpr int lo = i >= 2 ? -3 : -2;
-    auto bth = [&](int o) { return i >= 2 ? rc.bth_p[o] : rc.bth_m[o]; };
-    dth = products(bth(0), buf[cN + lo * LXT], bth(1), buf[cN + (lo + 1) * LXT]);
-    static_for<2, 6>([&](auto oc) {
-      constexpr int o = decltype(oc)::value;
-      dth = fused(bth(o), buf[cN + (lo + o) * LXT], dth);
-    });
-    adv[k] = advection<T>(theta_first(i, j), fuse_constant(i, j), dth, dph, T(vel(i)),
-                          T(-vel(j)) * inv_Jdph, n_ref * T(rest_offset<T>(k)),
-                          i >= 2 ? rc.bsum_p : rc.bsum_m);
+      dph = uw5_difference<T, j >= 2>([&](int o) { return buf[cN + o]; });
+      // theta direction: sum_o uw5(o) J_{q+o} / (r J_q dtheta) f_{q+o}
+      constexpr int lo = i >= 2 ? -3 : -2;
+      auto bth = [&](int o) { return i >= 2 ? rc.bth_p[o] : rc.bth_m[o]; };
+      dth = products(bth(0), buf[cN + lo * LXT], bth(1), buf[cN + (lo + 1) * LXT]);
+      static_for<2, 6>([&](auto oc) {
+        constexpr int o = decltype(oc)::value;
+        dth = fused(bth(o), buf[cN + (lo + o) * LXT], dth);
+      });
+      adv[k] = advection<T>(theta_first(i, j), fuse_constant(i, j), dth, dph, T(vel(i)),
+                            T(-vel(j)) * inv_Jdph, n_ref * T(rest_offset<T>(k)),
+                            i >= 2 ? rc.bsum_p : rc.bsum_m);
     }
     if (ring) {
       const T fr = buf[cR];
@@ -2088,9 +2088,11 @@ double state_bytes(const tlb_grid* g) {
 int streaming(const tlb_grid* g) { return streaming_level(state_bytes(g), g->elem, whole_lines(g)); }
 
 // The small-grid kernel runs grids of at most this many 64-node row segments (not WENO-5, whose
-// arithmetic outweighs the latencies).  Times per step in us, tiles / small-grid kernel: FP32, 960
-// segments 24.1 / 19.0, 1285 24.4 / 22.9, 1800 28.3 / 30.9; FP64, 320 segments 31.7 / 24.1, 640
-// 31.7 / 30.8, 960 33.8 / 38.1.
+// arithmetic outweighs the latencies).  Times per step in us, tiles / small-grid kernel: FP32, 640
+// segments 22.9 / 17.7, 1280 24.3 / 22.4, 1285 24.5 / 24.0, 1600 25.0 / 27.9; FP64, 320 segments 29.8 /
+// 23.6, 640 31.7 / 31.6, 960 33.0 / 39.1.  With the fourth-order variant, whose prepass is the same:
+// FP32, 640 segments 32.5 / 27.1, 1280 34.6 / 32.6, 1285 35.0 / 37.4; FP64, 320 segments 39.4 / 31.4,
+// 640 42.3 / 41.6, 960 49.0 / 49.8.
 constexpr long long small_rows(size_t elem) { return elem == 4 ? 1280 : 640; }
 
 long long row_segments(const tlb_grid* g) {

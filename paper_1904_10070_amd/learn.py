@@ -39,8 +39,8 @@ def _steps(t, dt):
 
 
 def coarse_grid(pc, precision=32):
-    """A coarse grid with the stage kernel's tile height chosen by the autotuner (small grids
-    prefer short tiles: more workgroups in flight)."""
+    """A coarse grid with the stage kernel's tile height chosen by the autotuner (grids small enough
+    for the kernel without tiles, 128 x 320 among them, keep the default height)."""
     g = TorusGrid(pc, precision)
     g.tile_rows = g.autotune()
     return g
